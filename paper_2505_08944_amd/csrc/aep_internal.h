@@ -32,31 +32,22 @@ struct WeightDesc {
 static_assert(sizeof(WeightDesc) == 48, "WeightDesc layout");
 
 // One FFN group of a drained batch, written by the plan kernel.  A group's
-// rows are covered by up to three row-tile families (bf16 / fp8 weights),
-// chosen per FFN stage (0: gate/up, 1: down): "big" 256-row tiles over the
-// full 256-row blocks, plus one more for a remainder above 128 rows (above
-// 192 rows in a stage where the extra big tiles would start another round
-// of the grid and that has fewer than 4 rounds; never in a cold batch), then
-// "medium" 128-row tiles and at most one "small" 64-row tile over the
-// remainder.  In a cold batch a remainder above 128 rows takes one "tall"
-// 256-row tile (kTallBM) in family 1 instead (h1 = kTallBM), so a cold
-// expert's weights are streamed once.  f32 weights use the big family alone,
-// with 64-row tiles.  In stage s, family 0 covers rows [0, nrt[s][0] * 256),
-// family 1 [row1[s], row1[s] + nrt[s][1] * h1[s]) and family 2 [row2[s],
-// row2[s] + nrt[s][2] * 64), clamped to n.  t0[s * 3 + f] is the group's first
-// tile id in family f of stage s.
+// rows are covered by row tiles of up to three families (bf16 / fp8 weights):
+// family 0 (256 rows) over its full 256-row blocks and a remainder above 128
+// rows, else one tile of family 1 (128 rows) or 2 (64 rows) over the
+// remainder, from row row1 on.  f32 weights use family 0 alone, with 64-row
+// tiles.  t0[s * 3 + f] is the group's first tile id in family f of FFN stage
+// s (0: gate/up, 1: down).
 struct GroupDesc {
-  int32_t n;          // rows
-  int32_t x_row0;     // first row in x_perm
-  int32_t y_row0;     // first row in h and y
-  int32_t t0[6];      // first tile id per (stage, family)
-  int32_t nrt[2][3];  // row tiles per (stage, family): big, medium (or tall), small
-  int32_t row1[2];    // first row of family 1 per stage (family 0 starts at row 0)
-  int32_t row2[2];    // first row of family 2 per stage
-  int32_t h1[2];      // rows per family-1 tile per stage: kMedBM, or kTallBM in a cold batch
+  int32_t n;        // rows
+  int32_t x_row0;   // first row in x_perm
+  int32_t y_row0;   // first row in h and y
+  int32_t t0[6];    // first tile id per (stage, family)
+  int32_t nrt[3];   // row tiles per family
+  int32_t row1;     // first row of the family 1 or 2 tile
   int32_t pad[3];
 };
-static_assert(sizeof(GroupDesc) == 96, "GroupDesc layout");
+static_assert(sizeof(GroupDesc) == 64, "GroupDesc layout");
 
 // Device error flag bits.
 constexpr int32_t kErrNonFinite = 1;
@@ -72,29 +63,21 @@ constexpr int kDirectPrefixBlocks = 64;  // router workgroups whose appends sum 
 constexpr int kMaxTopK = 8;
 constexpr int kMaxGroups = 1024;
 
-// FFN tiling (bf16 / fp8 weights): tiles of BM rows x BN columns; gate/up
-// tiles cover BN/2 features of gate and the same BN/2 of up.
+// FFN tiling (bf16 / fp8 weights): tiles of kBM >> family rows x kBN columns;
+// gate/up tiles cover kBN / 2 features of gate and the same of up.
 constexpr int kBM = 256;
 constexpr int kBN = 256;
 constexpr int kBK = 64;
-constexpr int kSmallBM = 64;            // small-family tiles: 64 rows ...
-constexpr int kSmallBN = 128;           // ... x 128 columns (gate/up: 64 features)
-constexpr int kSmallBN8 = 256;          // ... x 256 columns with fp8 weights
-constexpr int kMedBM = 128;             // medium-family tiles: 128 rows ...
-constexpr int kMedBN = 128;             // ... x 128 columns
-constexpr int kTallBM = 256;            // family 1 of a cold batch: 256 rows x kMedBN columns
-// Split-K of an FFN launch with at most half a grid of tiles: up to kMaxSplit
-// pieces of at least kMinSplitSteps K steps each per tile, for launches of at
-// most kSplitCounters tiles; kSplitPartBytes is one piece's partial sums of a
-// big tile (the largest family).
-constexpr int kMaxSplit = 4;
+constexpr int kFfnLds = 160 * 1024;  // LDS of one FFN workgroup (the CU's)
+// Split-K of the last, partial round of an FFN launch's tiles: up to
+// kMaxSplit pieces of at least kMinSplitSteps K steps each per tile, at most
+// kSplitCounters such tiles.
+constexpr int kMaxSplit = 8;
 constexpr int kMinSplitSteps = 8;
 constexpr int kSplitCounters = 1024;
-constexpr int64_t kSplitPartBytes = (int64_t)kBM * kBN * 4;
-// The partial sums' area of a context: 128 big-tile pieces (a launch of 64
-// big tiles splits in 2, one of 128 small tiles in 2, 32 big tiles in 4;
-// the kernel lowers n_split until a launch's pieces fit).
-constexpr int64_t kSplitBytes = 128 * kSplitPartBytes;
+// The partial sums' area of a context: 128 parts of a 256-row tile (a tile of
+// n pieces needs n - 1 parts; the kernel picks a split that fits).
+constexpr int64_t kSplitBytes = 128 * (int64_t)kBM * kBN * 4;
 // f32 path
 constexpr int kBM32 = 64;
 constexpr int kBN32 = 64;
@@ -136,22 +119,19 @@ hipError_t launch_enqueue_rows(const char* rows, int64_t row_bytes, const int32_
                                int k, int expert, int E, const int32_t* depth_cur,
                                int32_t* depth_nxt, QEntry* q, int64_t q_stride, int32_t* err,
                                hipStream_t s);
-// tile_totals[6] and nt[6] (column tiles per row tile), index stage * 3 +
-// family (stage 0 gate/up, 1 down; family 0 big, 1 medium, 2 small).
-// med_bm = small_bm = 0 disables the two smaller families (every row in big
-// tiles of big_bm).  num_cu: a batch with fewer full big gate/up tiles than
-// CUs puts no remainder in a big tile.
+// tile_totals[6]: tiles per (stage, family), index stage * 3 + family (stage
+// 0 gate/up, 1 down).  nt[2]: column tiles per row tile of each stage.
+// bm: rows of a family 0 tile; families: 3, or 1 (f32: every row in family 0).
 // only_expert >= 0: drain that expert's queue alone (every other group gets
 // 0 rows and keeps its queue).  depth is the current half of the layer's
 // depth ping-pong, depth_other the other one; both are cleared for the
 // drained experts.
 // tile_group [2][tile_cap]: the group of each tile of the gate/up (row 0) and
-// down (row 1) launch, tiles numbered big family first, then medium, small;
+// down (row 1) launch, tiles numbered family by family;
 // tile_cap bounds either launch's tile count.
 hipError_t launch_plan(int E, int S, int n_tokens, int k, int only_expert, int32_t* depth,
                        int32_t* depth_other, int32_t* counts, int32_t* offsets, GroupDesc* groups,
-                       int32_t* tile_totals, const int* nt, int big_bm, int med_bm, int small_bm,
-                       int num_cu, int32_t* tile_group, int64_t tile_cap, int32_t* pos, float* posw,
+                       int32_t* tile_totals, const int* nt, int bm, int families, int32_t* tile_group, int64_t tile_cap, int32_t* pos, float* posw,
                        hipStream_t s);
 // N bounds the routed rows (the exact count is offsets[E] on the device);
 // pos == nullptr skips the (token, slot) -> row map.
@@ -170,7 +150,7 @@ hipError_t launch_pool_release(int act_dtype, float* pool, int32_t* live, int32_
 // stage's tile count (the exact count is on the device); tile_group is that
 // stage's row of the plan's tile -> group map.  split_slots (split_bytes
 // bytes) holds the split-K partial sums and split_cnt [kSplitCounters] the
-// pieces finished per tile, zero before the launch and left zero (bf16 / fp8
+// arrivals per split tile, zero before the launch and left zero (bf16 / fp8
 // weights; split_slots == nullptr: no split).
 // clk != nullptr: workgroup w < clk_n writes its elapsed (s_memtime,
 // s_memrealtime) ticks to clk[2w], clk[2w + 1] (bf16 / fp8 weights only).

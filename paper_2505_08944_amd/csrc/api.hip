@@ -100,43 +100,28 @@ namespace {
 
 using Ctx = aep_ctx;
 
-// Tiling of the FFN launches: nt[6] = column tiles per row tile, index
-// stage * 3 + family (stage 0 gate/up, 1 down; family big, medium, small),
-// and the row-tile heights.  f32 uses 64 x 64 tiles only; bf16 and fp8
-// weights use 256 x 256 big tiles, 128 x 128 medium and 64 x 128 small ones
-// (64 x 256 with fp8 weights).
-void tiling(const Ctx& c, int nt[6], int* big_bm, int* med_bm, int* small_bm) {
+// Tiling of the FFN launches: nt[2] = column tiles per row tile of gate/up and
+// down, the rows of a family 0 tile and the number of row-tile families.
+// f32 uses 64 x 64 tiles only; bf16 and fp8 weights use tiles of 256, 128 and
+// 64 rows x 256 columns.
+void tiling(const Ctx& c, int nt[2], int* bm, int* families) {
   const int d = c.cfg.d_model, f = c.cfg.d_ffn;
   auto cdiv = [](int a, int b) { return (a + b - 1) / b; };
-  if (c.cfg.act_dtype == AEP_F32) {
-    nt[0] = nt[1] = nt[2] = cdiv(f, kBN32);
-    nt[3] = nt[4] = nt[5] = cdiv(d, kBN32);
-    *big_bm = kBM32;
-    *med_bm = *small_bm = 0;
-  } else {
-    nt[0] = cdiv(f, kBN / 2);
-    nt[1] = cdiv(f, kMedBN / 2);
-    const int sbn = c.cfg.w_dtype == AEP_FP8_E4M3 ? kSmallBN8 : kSmallBN;
-    nt[2] = cdiv(f, sbn / 2);
-    nt[3] = cdiv(d, kBN);
-    nt[4] = cdiv(d, kMedBN);
-    nt[5] = cdiv(d, sbn);
-    *big_bm = kBM;
-    *med_bm = kMedBM;
-    *small_bm = kSmallBM;
-  }
+  const bool f32 = c.cfg.act_dtype == AEP_F32;
+  nt[0] = f32 ? cdiv(f, kBN32) : cdiv(f, kBN / 2);
+  nt[1] = f32 ? cdiv(d, kBN32) : cdiv(d, kBN);
+  *bm = f32 ? kBM32 : kBM;
+  *families = f32 ? 1 : 3;
 }
 
 // Upper bound of one FFN launch's tiles for a batch of N routed rows and T
-// tokens: every group's rows in big tiles (one partial big row tile per
-// non-empty group), plus at most 2 medium and 1 small row tiles per group.
+// tokens: the full blocks of family 0 and one more row tile per non-empty
+// group.
 int64_t tile_bound(const Ctx& c, int stage, int64_t N, int64_t T) {
-  int nt[6], big_bm, med_bm, small_bm;
-  tiling(c, nt, &big_bm, &med_bm, &small_bm);
-  const int64_t E = c.cfg.n_experts, S = c.cfg.n_shared, G = E + S;
-  const int64_t big_rows = N / big_bm + std::min<int64_t>(E, N) + S * ((T + big_bm - 1) / big_bm);
-  const int* ns = nt + 3 * stage;
-  return big_rows * ns[0] + (small_bm ? G * (2 * (int64_t)ns[1] + ns[2]) : 0);
+  int nt[2], bm, families;
+  tiling(c, nt, &bm, &families);
+  const int64_t E = c.cfg.n_experts, S = c.cfg.n_shared;
+  return (N / bm + std::min<int64_t>(E, N) + S * ((T + bm - 1) / bm)) * nt[stage];
 }
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -557,8 +542,8 @@ aep_status aep_rebatch(aep_ctx* ctx, int32_t layer, aep_batch* out, void* stream
   if (L.rows == 0 && !(c->cfg.n_shared > 0 && L.tokens > 0)) return AEP_ERR_EMPTY;
   for (int g = 0; g < c->G; ++g)
     if (!L.have_w[g]) return AEP_ERR_STATE;
-  int nt[6], big_bm, med_bm, small_bm;
-  tiling(*c, nt, &big_bm, &med_bm, &small_bm);
+  int nt[2], bm, families;
+  tiling(*c, nt, &bm, &families);
   hipStream_t s = as_stream(stream);
   const int E = c->cfg.n_experts, S = c->cfg.n_shared, k = c->cfg.top_k;
   int32_t* counts = c->at<int32_t>(c->off_counts);
@@ -566,8 +551,8 @@ aep_status aep_rebatch(aep_ctx* ctx, int32_t layer, aep_batch* out, void* stream
   int32_t* pos = c->at<int32_t>(c->off_pos);
   float* posw = c->at<float>(c->off_posw);
   if (launch_plan(E, S, L.tokens, k, -1, c->depth(layer, L.cur), c->depth(layer, L.cur ^ 1), counts, offsets,
-                  c->at<GroupDesc>(c->off_groups), c->at<int32_t>(c->off_tiles), nt, big_bm, med_bm,
-                  small_bm, c->num_cu, c->at<int32_t>(c->off_tilegrp), c->tile_cap, pos, posw, s) != hipSuccess)
+                  c->at<GroupDesc>(c->off_groups), c->at<int32_t>(c->off_tiles), nt, bm, families,
+                  c->at<int32_t>(c->off_tilegrp), c->tile_cap, pos, posw, s) != hipSuccess)
     return AEP_ERR_DEVICE;
   const int64_t row_bytes = (int64_t)c->cfg.d_model * c->esz;
   if (launch_gather(c->q(layer), c->tmax(), offsets, E, L.rows, L.tokens, S > 0, c->tokrow(layer),
@@ -605,15 +590,15 @@ aep_status aep_rebatch_expert(aep_ctx* ctx, int32_t layer, int32_t expert, aep_b
   const int64_t nb = std::min(L.bound[expert], L.rows);
   if (nb == 0) return AEP_ERR_EMPTY;
   if (!L.have_w[expert]) return AEP_ERR_STATE;
-  int nt[6], big_bm, med_bm, small_bm;
-  tiling(*c, nt, &big_bm, &med_bm, &small_bm);
+  int nt[2], bm, families;
+  tiling(*c, nt, &bm, &families);
   hipStream_t s = as_stream(stream);
   const int E = c->cfg.n_experts, k = c->cfg.top_k;
   int32_t* counts = c->at<int32_t>(c->off_counts);
   int32_t* offsets = c->at<int32_t>(c->off_offsets);
   if (launch_plan(E, 0, 0, k, expert, c->depth(layer, L.cur), c->depth(layer, L.cur ^ 1), counts, offsets,
                   c->at<GroupDesc>(c->off_groups),
-                  c->at<int32_t>(c->off_tiles), nt, big_bm, med_bm, small_bm, c->num_cu,
+                  c->at<int32_t>(c->off_tiles), nt, bm, families,
                   c->at<int32_t>(c->off_tilegrp), c->tile_cap, nullptr, nullptr, s) != hipSuccess)
     return AEP_ERR_DEVICE;
   const int64_t row_bytes = (int64_t)c->cfg.d_model * c->esz;

@@ -4,44 +4,41 @@
 //   gate/up:  h[r, c] = silu(x_r . W_gate[c]) * (x_r . W_up[c])   (K = d)
 //   down:     y[r, c] = h_r . W_down[c]                            (K = f)
 //
-// The plan kernel laid the tiles of all groups (experts) end to end in three
-// row-tile families, split per stage: 256 x 256 tiles for the full 256-row
-// blocks of an expert (and for a remainder above 128 rows, unless that would
-// start another round of the grid in a short stage), then 128 x 128 medium
-// tiles (256 x 128 tall ones for a cold batch's remainders above 128 rows)
-// and 64 x 128 small tiles (64 x 256 with fp8 weights) for the ragged row
-// tails and cold experts.  One launch covers a whole skewed batch, from a
-// 1-row expert to the hottest one:
-// every big tile first, then the smaller ones, which also fill the tail of
-// the big family.  The workgroup -> tile map is XCD aware: hardware
-// dispatches workgroups round robin over the 8 XCDs, so workgroup w works on
-// slot (w % 8) * (grid / 8) + w / 8, giving each XCD (and its L2) a
-// contiguous run of tiles, and the big tiles of a group are ordered in panels
-// of 8 column tiles (4 in the down launch) so that such a run is a compact
-// block of row and column tiles.
+// bf16 / fp8-weight path: 512-thread workgroups, one per CU, K step 64, tiles
+// of 256 columns (gate/up: 128 features of W_gate and the same 128 of W_up)
+// and 256, 128 or 64 rows.  The plan kernel covers a group's rows with full
+// 256-row tiles and one remainder tile of the smallest height that holds the
+// rest, so an expert's weights are read ceil(rows / 256) times.  It lays the
+// tiles of all groups end to end, family by family; this kernel deals them to
+// the workgroups (see Sched).
 //
-// bf16 / fp8-weight path: 256-thread workgroups, K step 64, four waves each
-// owning a quadrant of the tile computed with v_mfma_f32_32x32x16_bf16 (f32
-// accumulate).  Tiles move from global memory straight into LDS (no staging
-// registers) through a ring of stages; the loads of later K steps are in
-// flight while the current one is multiplied, and the refill of a freed
-// stage is spread over the MFMAs that follow instead of issued as a block.  Gate/up tiles hold BN/2
-// features of W_gate and the same BN/2 of W_up, interleaved per wave quadrant,
-// so each lane finds the gate and up accumulator of the same (row, feature)
-// in its own registers and applies the SiLU-and-multiply epilogue without any
-// exchange.  fp8 (OCP e4m3fn) weights stay fp8 in LDS and are widened to bf16
-// exactly when read into MFMA operands; the per-channel scale multiplies the
-// f32 accumulator in the epilogue.
+// Ping-pong.  The eight waves form two groups of four; a SIMD runs one wave
+// of each.  A workgroup barrier ends every slot, and in a slot one group
+// issues the MFMAs of its next phase while the other reads that phase's
+// operands from LDS and issues the direct-to-LDS loads of a later K step; the
+// next slot swaps the roles.  The matrix cores therefore always have a wave
+// with its operands in registers, and the memory slot's latencies hide behind
+// the other group's MFMAs.  Measured on the hot loop (8192 rows, d = 4096,
+// f = 14336): 2220 / 2144 cycles per K step in gate/up / down against the
+// 2048 its MFMAs take; one wave per SIMD (four waves of 128 x 128, the operand
+// reads and refills spread between the MFMAs) took about 3000.  At that duty
+// the shader clock is what the power limit leaves (1.5 - 1.65 GHz), which is
+// why the MFMA shape matters: 16x16x32 ran the same loop at 1.5 - 1.6 GHz,
+// 32x32x16 (twice the accumulator traffic per operation) at 1.3 - 1.4.
 //
 // f32 path (f32 activations and weights): 64 x 64 tiles, 4 x 4 outputs per
 // thread with FMA, for the fp32 workload.
+#include <limits.h>
+
 #include "aep_device.h"
 #include "aep_internal.h"
 
 namespace aep {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x2v_t __attribute__((ext_vector_type(2)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 
 struct FfnParams {
   const GroupDesc* groups;
@@ -60,47 +57,13 @@ struct FfnParams {
   int clk_n;
 };
 
-// Accumulator layout of v_mfma_f32_32x32x16_bf16: lane l, register r holds
-// column l % 32 and row 8 * (r / 4) + 4 * (l / 32) + r % 4.
-__device__ __forceinline__ int c_row(int lane, int r) {
-  return ((r >> 2) << 3) + ((lane >> 5) << 2) + (r & 3);
-}
 
-// Tile order inside one group's nrow x ncol grid of big tiles: panels of
-// PANEL column tiles, row tiles one after another inside a panel, the
-// columns of a row tile adjacent.  The persistent grids hand each XCD runs of
-// consecutive tile ids (32 for 256 workgroups), so an XCD works on a compact
-// block of tiles (4 x 8 for gate/up, 8 x 4 for down): per K step its L2 sees
-// a few row bands of A and column bands of B instead of every row band of the
-// group against one column band.  Down launches have few column tiles
-// (d / 256) and long K; panels of 4 measured 1-4% faster there, panels of 8
-// faster for gate/up on single experts.
-template <int PANEL>
-__device__ __forceinline__ void panel_decode(int local, int nrow, int ncol, int& rt, int& ct) {
-  const int per = PANEL * nrow;
-  const int pi = local / per;
-  const int within = local - pi * per;
-  const int w = min(PANEL, ncol - pi * PANEL);  // the last panel may be narrower
-  rt = within / w;
-  ct = pi * PANEL + (within - rt * w);
-}
-
-// ------------------------------------------------- direct-to-LDS MFMA tiles
-// Tiles move from global memory straight into LDS (buffer_load_dwordx4 with
-// the lds bit: 64 lanes x 16 bytes into 1 KB of consecutive LDS, no staging
-// registers),
-// through a ring of STAGES LDS buffers with a prefetch distance of
-// STAGES - 1 K steps.  LDS rows are not padded; a 16-byte chunk c of tile row r sits at position
-// c ^ s(r), where s spreads the 8 rows read together by one fragment read
-// over distinct banks (s(r) = r % 8 for 128-byte rows, (r / 2) % 4 for
-// 64-byte rows).  Each lane picks the global chunk that belongs at its fixed
-// LDS position, so the swizzle costs nothing at load time.
 typedef __attribute__((address_space(3))) void* lds_vptr;
-typedef const __attribute__((address_space(1))) void* glb_vptr;
 
 // A raw buffer resource over [base, base + bytes): stride 0, 32-bit data
 // format, every access bounds-checked against bytes (an access past the end
-// reads zeros and writes nothing).  The fields are uniform (SGPRs).
+// reads zeros without touching memory and writes nothing).  The fields are
+// uniform (SGPRs).
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ i32x4_t make_rsrc(const void* base, uint32_t bytes) {
   const uint64_t a = (uint64_t)(uintptr_t)base;
@@ -114,753 +77,764 @@ __device__ __forceinline__ i32x4_t make_rsrc(const void* base, uint32_t bytes) {
 
 // One direct buffer -> LDS load: lane l reads the 16 bytes at byte offset
 // voff + soff of the resource and writes them to lds_addr + 16 * l (M0 holds
-// lds_addr).  The per-step K offset rides in the scalar soff, so a load costs
-// no vector address arithmetic.  Issued through inline asm so that the
-// compiler does not see an LDS write it cannot disambiguate (it would
-// otherwise wait for every outstanding load before each LDS read); the
-// kernel orders these loads itself with wait_vmcnt + barriers.
+// lds_addr).  Issued through inline asm so that the compiler does not see an
+// LDS write it cannot disambiguate (it would otherwise wait for every
+// outstanding load before each LDS read); the kernel orders these loads
+// itself with wait_vmcnt + barriers.
 __device__ __forceinline__ void dload16(i32x4_t rsrc, uint32_t voff, uint32_t soff, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %3\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(rsrc),
                "s"(soff), "s"(__builtin_amdgcn_readfirstlane(lds_addr))
                : "memory", "m0");
 }
 
-// s_waitcnt with only vmcnt constrained (gfx9 encoding).
+// A wave-uniform value, in a scalar register whatever unit computed it.
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// s_waitcnt with only vmcnt (or only lgkmcnt) constrained (gfx9 encoding).
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   __builtin_amdgcn_s_waitcnt((N & 0xf) | ((N >> 4) << 14) | (0x7 << 4) | (0xf << 8));
 }
+__device__ __forceinline__ void wait_lgkm0() { __builtin_amdgcn_s_waitcnt(0xf | (3 << 14) | (0x7 << 4)); }
 
-// Wait until at most MUL * per loads are outstanding, per in [LO, HI] (the
-// wave's loads per K step; the immediate must be a constant, hence the
-// uniform branch ladder).
-template <int MUL, int LO, int HI>
-__device__ __forceinline__ void wait_steps(int per) {
-  if constexpr (MUL == 0 || LO == HI) {
-    wait_vmcnt<MUL * LO>();
-  } else {
-    if (per <= LO)
-      wait_vmcnt<MUL * LO>();
-    else
-      wait_steps<MUL, LO + 1, HI>(per);
-  }
+// Workgroup barrier that orders nothing but the instruction stream: the
+// waits before it are explicit.
+__device__ __forceinline__ void slot_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
 }
 
-// One output tile of BM rows x BN columns (gate/up: BN/2 features of gate and
-// the same BN/2 of up) at row m0 of group gd, column tile nti.  Four waves in
-// a 2 x 2 grid, each owning a (BM/2) x (BN/2) block of 32 x 32 MFMA
-// fragments.  STAGES LDS buffers form the ring (prefetch distance STAGES - 1
-// K steps of 64); a stage holds the A tile (BM rows x 128 bytes, bf16) and
-// the B tile (BN rows x 128 bytes for bf16 weights, x 64 bytes for fp8).
-//
-// fp8 weights (FP8): B stays e4m3 in LDS.  One 16-byte read gives a lane 16
-// consecutive k of its row; lanes 0-31 read k-chunk 2m, lanes 32-63 chunk
-// 2m + 1 (K elements 32m .. 32m + 31), and the two halves of the read feed
-// two MFMAs after an exact e4m3 -> bf16 conversion.  The A reads follow the
-// same assignment of k to lanes (bf16 chunks 4m + 2h and 4m + 2h + 1 for
-// lane half h), so every MFMA still pairs equal k; per-channel scales are
-// applied in the epilogue.
-template <bool GATED, bool FP8, int BM, int BN, int STAGES, int BSTAGES, int CAP>
-__device__ __forceinline__ void dl_tile(const FfnParams& p, unsigned char* smem, uint32_t lds_base,
-                                        const GroupDesc& gd, const WeightDesc& wd, int nti, int m0,
-                                        int rot_seed, int n_split = 1, int piece = 0, float* slot = nullptr,
-                                        int32_t* cnt = nullptr) {
-  constexpr int BKS = kBK;
-  constexpr int kRowA = BKS * 2;              // 128 bytes: one A row of one K step
-  constexpr int kRowB = FP8 ? BKS : BKS * 2;  // one B row of one K step
-  constexpr int kRplA = 1024 / kRowA;         // rows per direct load (8)
-  constexpr int kRplB = 1024 / kRowB;         // 8, or 16 for fp8
-  constexpr int kChB = kRowB / 16;            // 16-byte chunks per B row (8 or 4)
-  constexpr int TM = BM / 2, TN = BN / 2;     // wave tile
-  constexpr int MI = TM / 32, NI = TN / 32;   // 32 x 32 fragments per wave
-  constexpr int kNA = BM / kRplA / 4;         // direct loads per wave per K step: A
-  constexpr int kNB = BN / kRplB / 4;         // ... and B
-  constexpr int kTileA = BM * kRowA, kTileB = BN * kRowB, kStageB = kTileA + kTileB;
-  constexpr int kPerStep = kNA + kNB;
-  // Ring layout.  One ring (BSTAGES == STAGES): stage s holds A then B at
-  // s * kStageB.  Split rings (BSTAGES > STAGES, bf16 big tiles): STAGES A
-  // stages first, then BSTAGES B stages, so the weight tiles are prefetched
-  // further ahead than the activation tiles.
-  constexpr bool kSplit = BSTAGES != STAGES;
-  constexpr int kAStride = kSplit ? kTileA : kStageB;
-  constexpr int kBBase = kSplit ? STAGES * kTileA : kTileA;
-  constexpr int kBStride = kSplit ? kTileB : kStageB;
-  static_assert(!kSplit || (!FP8 && STAGES == 2 && BSTAGES == 3), "split rings: bf16, 2 A + 3 B stages");
-  constexpr int kLd = BN / 2 + 8;             // epilogue staging row stride (bf16)
-  static_assert(MI >= 1 && NI >= 2 && NI % 2 == 0, "wave tile");
-  static_assert(kNA >= 1 && kNB >= 1, "loads per wave");
-  static_assert(!GATED || kNB * kRplB == TN / 2, "a wave's B rows are all gate or all up rows");
-  static_assert(STAGES * kTileA + BSTAGES * kTileB <= CAP, "ring must fit the shared buffer");
-  static_assert(BM * kLd * 2 <= CAP, "epilogue staging must fit");
-  static_assert((STAGES - 1) * kPerStep < 64, "vmcnt range");
+// Tile order inside one group's nrow x ncol grid of 256-row tiles: panels of
+// PANEL column tiles, row tiles one after another inside a panel, the
+// columns of a row tile adjacent.  An XCD gets runs of 32 consecutive tiles,
+// so it works on a compact block of tiles (4 x 8 for gate/up, 8 x 4 for
+// down): per K step its L2 sees a few row bands of A and column bands of B.
+// Panels of 4 measured 1-4% faster in the down launch (few column tiles,
+// long K), panels of 8 in gate/up.
+template <int PANEL>
+__device__ __forceinline__ void panel_decode(int local, int nrow, int ncol, int& rt, int& ct) {
+  const int per = PANEL * nrow;
+  const int pi = local / per;
+  const int within = local - pi * per;
+  const int w = min(PANEL, ncol - pi * PANEL);  // the last panel may be narrower
+  rt = within / w;
+  ct = pi * PANEL + (within - rt * w);
+}
 
-  // The thread index goes through an empty asm so that the per-lane offsets
-  // derived from it are computed per tile instead of being hoisted out of the
-  // tile loop, where they would stay live across the K loop and be spilled.
+// ------------------------------------------------------------ work division
+// Tiles are numbered family by family (256, 128, 64 rows).  The first
+// `whole` of them -- full rounds of the grid -- are one work item each.  The
+// others, a partial round, would leave CUs idle: they are cut along K into
+// nsp[family] pieces (at least kMinSplitSteps steps each), whose f32 partial
+// sums meet in the workspace.  Items are dealt round by round; odd rounds in
+// reverse, so that a workgroup that got one of a round's larger items gets
+// one of the next round's smaller ones.
+struct Sched {
+  int b1, b2, total;  // first tile of families 1 and 2, and the number of tiles
+  int whole, items;
+  int nsp;            // pieces per tail tile: family f in bits 4f .. 4f + 3
+  __device__ __forceinline__ int first(int f) const { return f == 0 ? 0 : f == 1 ? b1 : f == 2 ? b2 : total; }
+  // first tail tile of family f and how many there are
+  __device__ __forceinline__ int tail0(int f) const { return max(first(f), whole); }
+  __device__ __forceinline__ int tail(int f) const { return max(0, first(f + 1) - tail0(f)); }
+  __device__ __forceinline__ int pieces(int f) const { return (nsp >> (4 * f)) & 15; }
+};
+
+// Relative cost of one K step of a tile per family: a 256-row step is bound
+// by its MFMAs, the smaller ones by the CU's load path (64, 48 and 40 KB per
+// step), and the cost of a split tile's partial sums in the same unit.
+__device__ __forceinline__ int step_cost(int f) { return f == 0 ? 8 : f == 1 ? 6 : 5; }
+
+__device__ __forceinline__ int fam_floats(int f) { return (kBM * kBN) >> f; }
+__device__ __forceinline__ int piece_cost(int f, int KT, int n) {
+  return (int)((float)(step_cost(f) * KT) * __builtin_amdgcn_rcpf((float)n)) + (n > 1 ? (40 + 20 * n) >> f : 0);
+}
+
+__device__ __forceinline__ int item_family(const Sched& s, int item) {
+  if (item < s.whole) return item < s.b1 ? 0 : (item < s.b2 ? 1 : 2);
+  const int j = item - s.whole;
+  const int m0 = s.tail(0) * s.pieces(0), m1 = s.tail(1) * s.pieces(1);
+  return j < m0 ? 0 : (j < m0 + m1 ? 1 : 2);
+}
+
+// Work item of workgroup slot lin (XCD-blocked: lin / (nwg / 8) is its XCD)
+// in round r, -1 for none.
+__device__ __forceinline__ int round_item(const Sched& s, int r, int nwg, int xcd, int xj) {
+  const int base = r * nwg;
+  const int cnt = s.items - base;
+  if (cnt <= 0) return -1;
+  const int lin = xcd * (nwg >> 3) + xj;
+  const int rl = (r & 1) ? nwg - 1 - lin : lin;
+  if (cnt >= nwg) return base + rl;
+  // a partial round: over all XCDs, unless the round before it was a mix of
+  // families; then the workgroups that had its smaller items come first
+  if (r > 0 && item_family(s, base - nwg) != item_family(s, base - 1)) return rl < cnt ? base + rl : -1;
+  const int q = (cnt + 7) >> 3;
+  const int idx = xcd * q + xj;
+  return xj < q && idx < cnt ? base + idx : -1;
+}
+
+// Pieces per tail tile: every combination of up to kMaxSplit pieces per
+// family is tried by one thread, which adds up the loads of a sample of
+// workgroups; the smallest maximum wins (fewest pieces on a tie).
+__device__ __forceinline__ void make_sched(Sched& s, const FfnParams& p, const int32_t* tot, int nwg, int KT,
+                                           int* lds) {
+  const int tid = threadIdx.x;
+  s.b1 = uni(tot[0]);
+  s.b2 = s.b1 + uni(tot[1]);
+  s.total = s.b2 + uni(tot[2]);
+  const int rem = uni(s.total % nwg);
+  s.whole = s.total - rem;
+  s.items = s.total;
+  s.nsp = 0x111;
+  // nothing to gain: no tail, a small share of many rounds, K too short
+  if (rem == 0 || s.whole >= 8 * nwg || KT < 2 * kMinSplitSteps || p.split_slots == nullptr) return;
+  const int n[3] = {1 + (tid & 7), 1 + ((tid >> 3) & 7), 1 + (tid >> 6)};
+  bool ok = true;
+  int64_t floats = 0;
+  int c[3], end[3], items = s.whole;
+#pragma unroll
+  for (int f = 0; f < 3; ++f) {
+    const int tl = s.tail(f);
+    if (n[f] > 1 && (tl == 0 || KT < n[f] * kMinSplitSteps)) ok = false;
+    floats += (int64_t)tl * ((n[f] - 1) * fam_floats(f));
+    items += tl * n[f];
+    end[f] = items;
+    c[f] = piece_cost(f, KT, n[f]);
+  }
+  if (floats * 4 > p.split_bytes || items - s.whole > 4 * nwg) ok = false;
+  unsigned key = 0xffffffffu;
+  if (ok) {
+    int worst = 0;
+    // the round before the tail counts: its items may differ in size
+    const int base0 = max(0, s.whole - nwg);
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+      const int lin = q * (nwg - 1) / 4;
+      int load = 0, at = lin;  // position within the round, reversed each time
+      for (int base = base0; base < items; base += nwg) {
+        const int it = base + at;
+        at = nwg - 1 - at;
+        load += it < s.whole ? step_cost(it < s.b1 ? 0 : it < s.b2 ? 1 : 2) * KT
+                : it < end[0] ? c[0] : it < end[1] ? c[1] : it < end[2] ? c[2] : 0;
+      }
+      worst = max(worst, load);
+    }
+    // smallest (cost, thread): lower thread ids have fewer pieces
+    key = (unsigned)min(worst, (1 << 22) - 1) * 512u + (unsigned)tid;
+  }
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) key = min(key, (unsigned)__shfl_xor((int)key, off));
+  if ((tid & 63) == 0) lds[tid >> 6] = (int)key;
+  __syncthreads();
+  unsigned best = 0xffffffffu;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) best = min(best, (unsigned)lds[w]);
+  __syncthreads();
+  const int pick = uni(best == 0xffffffffu ? 0 : (int)(best & 511u));
+  s.nsp = (1 + (pick & 7)) | (1 + ((pick >> 3) & 7)) << 4 | (1 + (pick >> 6)) << 8;
+#pragma unroll
+  for (int f = 0; f < 3; ++f) s.items += s.tail(f) * (s.pieces(f) - 1);
+}
+
+// One work item: `rows` rows of a group from row y_row0 (h and y) / x_row0
+// (x_perm) on, column tile nti, K steps [k0, k0 + kn).
+struct Item {
+  int g, nti, rows, y_row0, kn;  // what the epilogue needs
+  int x_row0, k0, rot;           // what the load stream needs as well
+};
+// Where a tail tile's item stands among its pieces.
+struct Piece {
+  int n, piece, cnt;  // pieces, this one, the tile's counter
+  int64_t slot;       // float offset of the tile's partial sums
+  int tile;
+};
+
+__device__ __forceinline__ Piece decode_piece(const Sched& s, int item, int f) {
+  Piece q{1, 0, 0, 0, item};
+  if (item < s.whole) return q;
+  int j = item - s.whole;
+  int64_t slot = 0;
+#pragma unroll
+  for (int e = 0; e < 2; ++e)
+    if (f > e) {
+      j -= s.tail(e) * s.pieces(e);
+      q.cnt += s.tail(e);
+      slot += (int64_t)s.tail(e) * (s.pieces(e) - 1) * fam_floats(e);
+    }
+  q.n = s.pieces(f);
+  const int ti = q.n == 1 ? j : uni(j / q.n);
+  q.piece = j - ti * q.n;
+  q.tile = s.tail0(f) + ti;
+  q.cnt += ti;
+  q.slot = slot + (int64_t)ti * (q.n - 1) * fam_floats(f);
+  return q;
+}
+
+template <bool GATED>
+__device__ __forceinline__ Item decode_item(const FfnParams& p, const Sched& s, int item, int f, int ncol, int KT) {
+  const Piece q = decode_piece(s, item, f);
+  Item it;
+  it.k0 = q.n == 1 ? 0 : uni(q.piece * KT / q.n);
+  it.kn = q.n == 1 ? KT : uni((q.piece + 1) * KT / q.n) - it.k0;
+  it.g = uni(p.tile_group[q.tile]);
+  const GroupDesc& gd = p.groups[it.g];
+  const int local = q.tile - s.first(f) - gd.t0[(GATED ? 0 : 3) + f];
+  int m0;
+  if (f == 0) {
+    int rt;
+    panel_decode<GATED ? 8 : 4>(local, gd.nrt[0], ncol, rt, it.nti);
+    m0 = rt * kBM;
+    it.rot = 0;
+  } else {
+    it.nti = local;
+    m0 = gd.row1;
+    // Smaller tiles stream weights: tiles that run together start their K
+    // walk at different steps, so they do not read the same DRAM channels
+    // in lockstep (a load-only probe: 0.68 -> 0.79 of peak bandwidth).
+    // 256-row tiles share bands with their neighbours in an XCD's L2, which
+    // a rotation would pull apart.
+    it.rot = uni((int)((7u * (unsigned)q.tile) % (unsigned)it.kn));
+  }
+  it.rows = uni(gd.n - m0);
+  it.x_row0 = uni(gd.x_row0 + m0);
+  it.y_row0 = uni(gd.y_row0 + m0);
+  it.nti = uni(it.nti);
+  return it;
+}
+
+// ------------------------------------------------------------- tile families
+// A K step's LDS stage holds the A rows (128 bytes each) in units of up to
+// 128 rows, then two B units of 128 rows (128 bytes each, 64 for fp8).  B
+// unit b, rows 32w .. 32w + 31 belong to wave column w: gate/up: 16 gate
+// features and the same 16 up features (tile features 32w + 16b ...), so a
+// lane holds both accumulators of an output; down: 32 output columns.
+// 16-byte chunk c of row r sits at position c ^ (r % 8) (fp8 B rows: c ^
+// ((r / 4) % 4)), which spreads the rows one read covers over the banks; the
+// loader lanes fetch the chunk that belongs at their fixed LDS position.
+template <bool FP8, int FAM>
+struct Fam {
+  static constexpr int kRows = kBM >> FAM;
+  static constexpr int kUnits = FAM == 0 ? 2 : 1;        // A units per stage
+  static constexpr int kUnitRows = kRows / kUnits;       // 128, 128, 64
+  static constexpr int RF = kUnitRows / 32;              // 16-row fragments per wave and unit
+  static constexpr int kA = kUnitRows * 128;             // bytes of an A unit
+  static constexpr int kB = 128 * (FP8 ? 64 : 128);      // bytes of a B unit
+  static constexpr int kStage = kUnits * kA + 2 * kB;
+  // ring depth: what fits 160 KB
+  static constexpr int kStages = FAM == 0 ? (FP8 ? 3 : 2) : FAM == 1 ? (FP8 ? 5 : 3) : (FP8 ? 6 : 4);
+  static constexpr int kLA = kUnitRows / 64;             // loads per wave: an A unit
+  static constexpr int kLB = FP8 ? 1 : 2;                // ... and a B unit
+  static_assert(kStages * kStage <= kFfnLds, "the ring fits the LDS");
+};
+
+// The load stream: which item's which K step the next stage is filled from.
+// It runs kStages steps ahead of the MFMAs, across items.
+struct Stream {
+  i32x4_t rsA, rsB;
+  int k, k0, kend, left;
+  __device__ __forceinline__ void next() {
+    --left;
+    k = k + 1 == kend ? k0 : k + 1;
+  }
+};
+
+template <bool GATED, bool FP8, int FAM>
+__device__ __forceinline__ void stream_set(Stream& st, const FfnParams& p, const Item& it, int wave) {
+  const int K = p.K;
+  const WeightDesc& wd = p.wtab[it.g];
+  const uint16_t* a = reinterpret_cast<const uint16_t*>(p.a) + (int64_t)(GATED ? it.x_row0 : it.y_row0) * K;
+  // rows past the group's end and columns past the matrix are out of the
+  // resources' range: they read as zeros, cost no traffic, and their outputs
+  // are not stored
+  st.rsA = make_rsrc(a, (uint32_t)min(it.rows, Fam<FP8, FAM>::kRows) * (uint32_t)K * 2u);
+  const unsigned char* w =
+      reinterpret_cast<const unsigned char*>(GATED ? ((wave & 1) ? wd.up : wd.gate) : wd.down);
+  const int c0 = it.nti * (GATED ? kBN / 2 : kBN);
+  constexpr uint32_t esz = FP8 ? 1u : 2u;
+  st.rsB = make_rsrc(w + (int64_t)c0 * K * esz, (uint32_t)(p.n_out - c0) * (uint32_t)K * esz);
+  st.k0 = it.k0;
+  st.kend = it.k0 + it.kn;
+  st.k = it.k0 + it.rot;
+  st.left = it.kn;
+}
+__device__ __forceinline__ void stream_null(Stream& st) {
+  // every lane is out of range (the scalar offset stays 0): no traffic
+  st.rsA.z = st.rsB.z = 0;
+  st.k = st.k0 = 0;
+  st.kend = 1;
+  st.left = INT_MAX;
+}
+
+// Runs the chain of items of family FAM that starts at round r of this
+// workgroup (whose item is `item`); leaves r and item at the first one of
+// another family (item < 0: none left).
+template <bool GATED, bool FP8, int FAM>
+__device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, unsigned char* smem,
+                                           uint32_t lds_base, int nwg, int xcd, int xj, int& r, int& item) {
+  using F = Fam<FP8, FAM>;
+  constexpr int RF = F::RF, NU = F::kUnits, NST = F::kStages;
   int tid = threadIdx.x;
+  // per-lane offsets are recomputed here instead of being kept live across
+  // the other families' loops
   asm volatile("" : "+v"(tid));
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;
-  const int K = p.K, KT0 = K / BKS, n_out = p.n_out;
-  // K steps of this work item: all of them, or piece `piece` of n_split
-  // (split-K): steps [k0, k0 + KT).
-  const int k0 = piece * KT0 / n_split, KT = (piece + 1) * KT0 / n_split - k0;
-  // K rotation: the tile walks its K steps starting at step rot and wrapping
-  // round (step j of the loop loads K step krot(j)).  Tiles that run at the
-  // same time start at different steps, so their weight streams do not hit
-  // the same DRAM channels in lockstep (a load-only probe of the cold-tile
-  // pattern: 0.68 -> 0.79 of peak HBM bandwidth).  rot_seed < 0: no rotation.
-  const int rot = rot_seed < 0 ? 0 : (int)((7u * (unsigned)rot_seed) % (unsigned)KT);
-  auto krot = [&](int j) { return k0 + (j + rot < KT ? j + rot : j + rot - KT); };
-  const uint16_t* A = reinterpret_cast<const uint16_t*>(p.a);
-  uint16_t* O = reinterpret_cast<uint16_t*>(p.out);
-  // chunk swizzles: spread the 8 rows one 128-byte bank window sees over
-  // distinct banks (r % 8 for 128-byte rows, (r / 2) % 4 for 64-byte rows)
-  auto swz_b = [](int r) { return kChB == 8 ? (r & 7) : ((r >> 1) & 3); };
-  // loaders: lane l fills chunk position l % chunks-per-row of row
-  // l / chunks-per-row of a load block with the global chunk that belongs
-  // there (load blocks start at multiples of 8 or 16 rows)
-  const int lda_row = lane >> 3;
-  const int lda_c = (lane & 7) ^ lda_row;
-  const int ldb_row = lane / kChB;
-  const int ldb_c = (lane % kChB) ^ swz_b(ldb_row);
-  // readers: fragment row and its swizzle
-  const int rd_row = lane & 31;
-  const int rd_sa = rd_row & 7;
-  const int rd_sb = swz_b(rd_row);
+  const int wm = wave & 1, wn = wave >> 1, grp = wave >> 2;
+  const int rr = lane & 15, hh = lane >> 4;
+  const int K = p.K, KT = K / kBK, n_out = p.n_out;
+  const int ncol = (n_out + (GATED ? kBN / 2 : kBN) - 1) / (GATED ? kBN / 2 : kBN);
 
-  const int arow0 = GATED ? gd.x_row0 : gd.y_row0;
-  const uint16_t* abase = A + (int64_t)(arow0 + m0) * K;
-  const int alast = gd.n - 1 - m0;
-  // A load blocks of this wave that hold rows of the group: blocks past the
-  // group's end are not loaded (their LDS rows hold stale data, their outputs
-  // are never stored), which saves the activation traffic of ragged and cold
-  // tiles.  Every K step of the tile issues the same number of loads per wave.
-  // Big bf16 tiles (two-stage ring) load every block: rows past the end
-  // repeat the last row, and the refill carries no per-load branches.
-  constexpr bool kAllA = !FP8 && STAGES == 2;
-  const int na_eff = kAllA ? kNA : __builtin_amdgcn_readfirstlane(
-      max(0, min(kNA, (alast + 1 - wave * kNA * kRplA + kRplA - 1) / kRplA)));
-  const int per_step = na_eff + kNB;
-  uint32_t aoff[kNA], boff[kNB];  // byte offsets into the two resources
+  // loader offsets: the same for every tile (the resources move)
+  uint32_t aoff[NU][F::kLA], boff[2][F::kLB];
 #pragma unroll
-  for (int i = 0; i < kNA; ++i)
-    aoff[i] = (uint32_t)(min((wave * kNA + i) * kRplA + lda_row, alast) * K + lda_c * 8) * 2u;
-  // B rows: a wave column's TN rows are TN/2 gate features then the same TN/2
-  // up features; a wave's B rows lie in one of the two halves.
-  const unsigned char* bmat;
-  {
-    const int br0 = wave * kNB * kRplB;
-    const bool up = GATED && (br0 % TN) >= TN / 2;
-    bmat = reinterpret_cast<const unsigned char*>(GATED ? (up ? wd.up : wd.gate) : wd.down);
-  }
-  // the group's rows from row m0 on, and the weight matrix (the host bounds
-  // both below 4 GiB)
-  const i32x4_t rsA = make_rsrc(abase, (uint32_t)(alast + 1) * (uint32_t)K * 2u);
-  const i32x4_t rsB = make_rsrc(bmat, (uint32_t)n_out * (uint32_t)K * (FP8 ? 1u : 2u));
+  for (int u = 0; u < NU; ++u)
 #pragma unroll
-  for (int i = 0; i < kNB; ++i) {
-    const int br = (wave * kNB + i) * kRplB + ldb_row;
-    int c = GATED ? nti * (BN / 2) + (br / TN) * (TN / 2) + (br % TN) % (TN / 2) : nti * BN + br;
-    c = min(c, n_out - 1);
-    boff[i] = (uint32_t)(c * K * (FP8 ? 1 : 2) + ldb_c * 16);
-  }
-
-#define DL_LOAD(kt_, st_)                                                                        \
-  do {                                                                                           \
-    const uint32_t sa_ = lds_base + (st_) * kAStride + wave * kNA * 1024;                         \
-    const uint32_t sb_ = lds_base + kBBase + (st_) * kBStride + wave * kNB * 1024;                \
-    _Pragma("unroll") for (int i = 0; i < kNA; ++i)                                              \
-        if (i < na_eff) dload16(rsA, aoff[i], (kt_) * kRowA, sa_ + i * 1024);                    \
-    _Pragma("unroll") for (int i = 0; i < kNB; ++i)                                              \
-        dload16(rsB, boff[i], (kt_) * kRowB, sb_ + i * 1024);                                    \
-  } while (0)
-  // bf16 weights: k-slice ks (16 k) of every fragment
-#define DL_READ(sa_, sb_, ks_, A_, B_)                                                           \
-  do {                                                                                           \
-    const unsigned char* aa_ = smem + (sa_) * kAStride;                                          \
-    const unsigned char* bb_ = smem + kBBase + (sb_) * kBStride;                                 \
-    const int ro_ = rd_row * kRowA + (((2 * (ks_) + (lane >> 5)) ^ rd_sa) << 4);                 \
-    _Pragma("unroll") for (int i = 0; i < MI; ++i) A_[i] =                                       \
-        *reinterpret_cast<const bf16x8_t*>(aa_ + (wm * TM + i * 32) * kRowA + ro_);              \
-    _Pragma("unroll") for (int j = 0; j < NI; ++j) B_[j] =                                       \
-        *reinterpret_cast<const bf16x8_t*>(bb_ + (wn * TN + j * 32) * kRowB + ro_);              \
-  } while (0)
-  // fp8 weights: half-step m (32 k): A for both MFMAs, raw e4m3 B
-#define DL_READ8(st_, m_, A1_, A2_, R_)                                                          \
-  do {                                                                                           \
-    const unsigned char* ab_ = smem + (st_) * kStageB; /* one ring */                            \
-    const int ca_ = 4 * (m_) + 2 * (lane >> 5);                                                  \
-    const int ra1_ = rd_row * kRowA + ((ca_ ^ rd_sa) << 4);                                      \
-    const int ra2_ = rd_row * kRowA + (((ca_ + 1) ^ rd_sa) << 4);                                \
-    const int rb_ = rd_row * kRowB + (((2 * (m_) + (lane >> 5)) ^ rd_sb) << 4);                  \
-    _Pragma("unroll") for (int j = 0; j < NI; ++j) R_[j] =                                       \
-        *reinterpret_cast<const uint4*>(ab_ + kTileA + (wn * TN + j * 32) * kRowB + rb_);        \
-    _Pragma("unroll") for (int i = 0; i < MI; ++i) {                                             \
-      A1_[i] = *reinterpret_cast<const bf16x8_t*>(ab_ + (wm * TM + i * 32) * kRowA + ra1_);      \
-      A2_[i] = *reinterpret_cast<const bf16x8_t*>(ab_ + (wm * TM + i * 32) * kRowA + ra2_);      \
-    }                                                                                            \
-  } while (0)
-  // e4m3 x 16 -> two bf16 x 8 operands (exact)
-#define DL_WIDEN(R_, B1_, B2_)                                                                   \
-  do {                                                                                           \
-    _Pragma("unroll") for (int j = 0; j < NI; ++j) {                                             \
-      const uint2 w0_ = e4m3x4_to_bf16x4(R_[j].x), w1_ = e4m3x4_to_bf16x4(R_[j].y);              \
-      const uint2 w2_ = e4m3x4_to_bf16x4(R_[j].z), w3_ = e4m3x4_to_bf16x4(R_[j].w);              \
-      B1_[j] = __builtin_bit_cast(bf16x8_t, make_uint4(w0_.x, w0_.y, w1_.x, w1_.y));             \
-      B2_[j] = __builtin_bit_cast(bf16x8_t, make_uint4(w2_.x, w2_.y, w3_.x, w3_.y));             \
-    }                                                                                            \
-  } while (0)
-#define DL_MMA(A_, B_)                                                                           \
-  do {                                                                                           \
-    _Pragma("unroll") for (int i = 0; i < MI; ++i) _Pragma("unroll") for (int j = 0; j < NI; ++j) \
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A_[i], B_[j], acc[i][j], 0, 0, 0);   \
-  } while (0)
-  // operand reads spread between the MFMAs
-  constexpr int kQ = MI * NI >= 4 ? 4 : MI * NI;
-#define DL_GROUP(sa_, sb_, ks_, An, Bn, Ac, Bc)                                                  \
-  do {                                                                                           \
-    DL_READ(sa_, sb_, ks_, An, Bn);                                                              \
-    DL_MMA(Ac, Bc);                                                                              \
-    _Pragma("unroll") for (int q_ = 0; q_ < kQ; ++q_) {                                          \
-      __builtin_amdgcn_sched_group_barrier(0x100, (MI + NI + kQ - 1) / kQ, 0);                   \
-      __builtin_amdgcn_sched_group_barrier(0x008, MI * NI / kQ, 0);                              \
-    }                                                                                            \
-    __builtin_amdgcn_sched_barrier(0);                                                           \
-  } while (0)
-  // fp8: one operand fragment of half-step m (index < NI: raw B, then A1, A2)
-#define DL_READ8_1(st_, m_, A1_, A2_, R_, idx_)                                                  \
-  do {                                                                                           \
-    const unsigned char* ab_ = smem + (st_) * kStageB;                                           \
-    const int ca_ = 4 * (m_) + 2 * (lane >> 5);                                                  \
-    if ((idx_) < NI) {                                                                           \
-      const int rb_ = rd_row * kRowB + (((2 * (m_) + (lane >> 5)) ^ rd_sb) << 4);                \
-      R_[(idx_)] = *reinterpret_cast<const uint4*>(ab_ + kTileA + (wn * TN + (idx_) * 32) * kRowB + rb_); \
-    } else if ((idx_) < NI + MI) {                                                               \
-      const int ra1_ = rd_row * kRowA + ((ca_ ^ rd_sa) << 4);                                    \
-      A1_[(idx_) - NI] = *reinterpret_cast<const bf16x8_t*>(ab_ + (wm * TM + ((idx_) - NI) * 32) * kRowA + ra1_); \
-    } else {                                                                                     \
-      const int ra2_ = rd_row * kRowA + (((ca_ + 1) ^ rd_sa) << 4);                              \
-      A2_[(idx_) - NI - MI] = *reinterpret_cast<const bf16x8_t*>(ab_ + (wm * TM + ((idx_) - NI - MI) * 32) * kRowA + ra2_); \
-    }                                                                                            \
-  } while (0)
-  // fp8: widen the raw B read in the previous group, then read the next
-  // half-step while the 2 * MI * NI MFMAs of this one run; the refill is
-  // spread over the step's MFMAs as in the deeper bf16 rings (DL_GROUP_S).
-#define DL_GROUP8_S(st_, m_, A1n, A2n, Rn, A1c, A2c, Rc, LK, LST, GB)                             \
-  do {                                                                                           \
-    constexpr int MN_ = MI * NI, M2_ = 2 * MI * NI, MT_ = 4 * MI * NI, LT_ = kNA + kNB,          \
-                  R_ = 2 * MI + NI;                                                              \
-    const uint32_t sa_ = lds_base + (LST) * kStageB + wave * kNA * 1024;                          \
-    const uint32_t sb_ = lds_base + (LST) * kStageB + kTileA + wave * kNB * 1024;                 \
-    DL_WIDEN(Rc, b1, b2);                                                                        \
-    __builtin_amdgcn_sched_barrier(0);                                                           \
-    _Pragma("unroll") for (int q_ = 0; q_ < M2_; ++q_) {                                         \
-      _Pragma("unroll") for (int r_ = q_ * R_ / M2_; r_ < (q_ + 1) * R_ / M2_; ++r_)             \
-          DL_READ8_1(st_, m_, A1n, A2n, Rn, r_);                                                 \
-      __builtin_amdgcn_sched_barrier(0);                                                         \
-      if (q_ < MN_)                                                                              \
-        acc[q_ / NI][q_ % NI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                         \
-            A1c[q_ / NI], b1[q_ % NI], acc[q_ / NI][q_ % NI], 0, 0, 0);                          \
-      else                                                                                       \
-        acc[(q_ - MN_) / NI][(q_ - MN_) % NI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(         \
-            A2c[(q_ - MN_) / NI], b2[(q_ - MN_) % NI], acc[(q_ - MN_) / NI][(q_ - MN_) % NI], 0, 0, 0); \
-      __builtin_amdgcn_sched_barrier(0);                                                         \
-      _Pragma("unroll") for (int l_ = 0; l_ < LT_; ++l_) {                                       \
-        if ((l_ * MT_) / LT_ == (GB) + q_) {                                                     \
-          const bool isa_ = l_ < 2 * kMinAB ? (l_ % 2 == 0) : (kNA > kNB);                       \
-          const int ix_ = l_ < 2 * kMinAB ? l_ / 2 : kMinAB + (l_ - 2 * kMinAB);                 \
-          if (isa_) {                                                                            \
-            if (ix_ < na_eff) dload16(rsA, aoff[ix_], (LK) * kRowA, sa_ + ix_ * 1024);           \
-          } else {                                                                               \
-            dload16(rsB, boff[ix_], (LK) * kRowB, sb_ + ix_ * 1024);                             \
-          }                                                                                      \
-        }                                                                                        \
-      }                                                                                          \
-      __builtin_amdgcn_sched_barrier(0);                                                         \
-    }                                                                                            \
-  } while (0)
-
-  // Two-stage rings (bf16 big tiles): the refill of the stage freed by a
-  // barrier (kNA + kNB loads per wave, the kNB weight blocks first, which
-  // measured 2-4% faster than alternating A and B blocks) goes out one load
-  // after every second MFMA of the 32 MFMAs that follow the barrier, i.e.
-  // over the first two operand groups of the step.
-  // Loads bunched after the barrier queue up at the address unit (four waves
-  // issue theirs at once) and stall the issuing wave, and with it its matrix
-  // pipe; spread this way they leave 32 MFMAs for the last load to land.
-  // The group's own operand reads (next slice) go out one per MFMA over its
-  // first MI + NI MFMAs.  GB: index of the group's first MFMA counted from
-  // the barrier.
-#define DL_READ1(sa_, sb_, ks_, A_, B_, idx_)                                                    \
-  do {                                                                                           \
-    const int ro_ = rd_row * kRowA + (((2 * (ks_) + (lane >> 5)) ^ rd_sa) << 4);                 \
-    if ((idx_) < MI)                                                                             \
-      A_[(idx_)] = *reinterpret_cast<const bf16x8_t*>(smem + (sa_) * kAStride +                  \
-                                                      (wm * TM + (idx_) * 32) * kRowA + ro_);    \
-    else                                                                                         \
-      B_[(idx_) - MI] = *reinterpret_cast<const bf16x8_t*>(                                      \
-          smem + kBBase + (sb_) * kBStride + (wn * TN + ((idx_) - MI) * 32) * kRowB + ro_);      \
-  } while (0)
-  // Deeper rings (the medium, small and tall families, fp8 big tiles): the
-  // refill of a freed stage is spread evenly over all MFMAs of the next step
-  // (refill list entry l, A and B blocks alternating while both remain, goes
-  // out after MFMA (l * MT) / LT of the step: MT MFMAs, LT loads), and the
-  // group's operand reads over its MFMAs.  Against one block of loads after
-  // the barrier: EP-share cold experts -10% (bf16 and fp8), fp8 4096-row
-  // expert -6..-11%.
-  constexpr int kMinAB = kNA < kNB ? kNA : kNB;
-#define DL_GROUP_S(st_, ks_, An, Bn, Ac, Bc, LK, LST, GB)                                        \
-  do {                                                                                           \
-    constexpr int MN_ = MI * NI, MT_ = 4 * MI * NI, LT_ = kNA + kNB, R_ = MI + NI;               \
-    const uint32_t sa_ = lds_base + (LST) * kAStride + wave * kNA * 1024;                         \
-    const uint32_t sb_ = lds_base + kBBase + (LST) * kBStride + wave * kNB * 1024;                \
-    _Pragma("unroll") for (int m_ = 0; m_ < MN_; ++m_) {                                         \
-      _Pragma("unroll") for (int r_ = m_ * R_ / MN_; r_ < (m_ + 1) * R_ / MN_; ++r_)             \
-          DL_READ1(st_, st_, ks_, An, Bn, r_);                                                   \
-      __builtin_amdgcn_sched_barrier(0);                                                         \
-      acc[m_ / NI][m_ % NI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                           \
-          Ac[m_ / NI], Bc[m_ % NI], acc[m_ / NI][m_ % NI], 0, 0, 0);                             \
-      __builtin_amdgcn_sched_barrier(0);                                                         \
-      _Pragma("unroll") for (int l_ = 0; l_ < LT_; ++l_) {                                       \
-        if ((l_ * MT_) / LT_ == (GB) + m_) {                                                     \
-          const bool isa_ = l_ < 2 * kMinAB ? (l_ % 2 == 0) : (kNA > kNB);                       \
-          const int ix_ = l_ < 2 * kMinAB ? l_ / 2 : kMinAB + (l_ - 2 * kMinAB);                 \
-          if (isa_) {                                                                            \
-            if (ix_ < na_eff) dload16(rsA, aoff[ix_], (LK) * kRowA, sa_ + ix_ * 1024);           \
-          } else {                                                                               \
-            dload16(rsB, boff[ix_], (LK) * kRowB, sb_ + ix_ * 1024);                             \
-          }                                                                                      \
-        }                                                                                        \
-      }                                                                                          \
-      __builtin_amdgcn_sched_barrier(0);                                                         \
-    }                                                                                            \
-  } while (0)
-  // Two-deep A ring (bf16 big tiles): the refill after the barrier that ends
-  // step kt goes out one load after every second MFMA of the 32 MFMAs that
-  // follow the barrier.  Split rings: the A blocks of step kt + 2 in the first
-  // group (the wait that ends the next step needs them), then the B blocks
-  // of step kt + 3.  One ring: the B blocks of step kt + 2 first, then its A
-  // blocks (weight-first measured 2-4% faster there).  GB: index of the
-  // group's first MFMA counted from the barrier.
-#define DL_GROUP_R(sa_, sb_, ks_, An, Bn, Ac, Bc, LKA, LSTA, LKB, LSTB, GB)                      \
-  do {                                                                                           \
-    static_assert(kNA == kNB && kNA + kNB == MI * NI, "one load per two MFMAs of two groups"); \
-    const uint32_t la_ = lds_base + (LSTA) * kAStride + wave * kNA * 1024;                        \
-    const uint32_t lb_ = lds_base + kBBase + (LSTB) * kBStride + wave * kNB * 1024;               \
-    _Pragma("unroll") for (int m_ = 0; m_ < MI * NI; ++m_) {                                     \
-      if (m_ < MI + NI) DL_READ1(sa_, sb_, ks_, An, Bn, m_);                                     \
-      __builtin_amdgcn_sched_barrier(0);                                                         \
-      acc[m_ / NI][m_ % NI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                           \
-          Ac[m_ / NI], Bc[m_ % NI], acc[m_ / NI][m_ % NI], 0, 0, 0);                             \
-      __builtin_amdgcn_sched_barrier(0);                                                         \
-      if (m_ % 2 == 1) {                                                                         \
-        const int l_ = ((GB) + m_) / 2;                                                          \
-        if (kSplit ? l_ < kNA : l_ >= kNB) {                                                     \
-          const int i_ = kSplit ? l_ : l_ - kNB;                                                 \
-          dload16(rsA, aoff[i_], (LKA) * kRowA, la_ + i_ * 1024);                                \
-        } else {                                                                                 \
-          const int i_ = kSplit ? l_ - kNA : l_;                                                 \
-          dload16(rsB, boff[i_], (LKB) * kRowB, lb_ + i_ * 1024);                                \
-        }                                                                                        \
-      }                                                                                          \
-      __builtin_amdgcn_sched_barrier(0);                                                         \
-    }                                                                                            \
-  } while (0)
-
-  f32x16_t acc[MI][NI];
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int j = 0; j < NI; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  // The previous tile's epilogue stores may still be in flight: the ring
-  // waits below count this tile's loads only, and since loads complete in
-  // issue order, older outstanding stores can only make those waits
-  // stricter (not waiting for the stores here: fine-grained layer gate/up
-  // -3%).
-  __syncthreads();  // every wave is done with the previous tile's LDS
-  if constexpr (kSplit) {
-    // Split rings: A(0), B(0), B(1), A(1); B(2) goes out with step 0's
-    // first operand group.  Step 0 has landed once only B(1) and A(1) are
-    // outstanding.
-    const uint32_t la_ = lds_base + wave * kNA * 1024;
-    const uint32_t lb_ = lds_base + kBBase + wave * kNB * 1024;
-    const int k0 = krot(0), k1 = krot(min(1, KT - 1));
-#pragma unroll
-    for (int i = 0; i < kNA; ++i) dload16(rsA, aoff[i], k0 * kRowA, la_ + i * 1024);
-#pragma unroll
-    for (int i = 0; i < kNB; ++i) dload16(rsB, boff[i], k0 * kRowB, lb_ + i * 1024);
-#pragma unroll
-    for (int i = 0; i < kNB; ++i) dload16(rsB, boff[i], k1 * kRowB, lb_ + kBStride + i * 1024);
-#pragma unroll
-    for (int i = 0; i < kNA; ++i) dload16(rsA, aoff[i], k1 * kRowA, la_ + kAStride + i * 1024);
-    wait_vmcnt<kNA + kNB>();
-  } else {
-#pragma unroll
-    for (int s = 0; s < STAGES; ++s) DL_LOAD(krot(min(s, KT - 1)), s);
-    wait_steps<STAGES - 1, kNB, kPerStep>(per_step);  // step 0 has landed (this wave's part)
-  }
-  __syncthreads();  // ... and every wave's part
-  // Step kt computes stage kt % STAGES.  Its last operand reads come before
-  // the barrier that ends the step, so right after that barrier the stage
-  // is refilled with step kt + STAGES: a step's loads have STAGES - 1 whole
-  // steps of MFMA work to land.  Past the last step the loads repeat the
-  // last step (never read).
-  if constexpr (kSplit) {
-    // A in 2 stages, B in 3: after the barrier that ends step kt, A(kt + 2)
-    // refills A stage kt % 2 (spread over the first group of step kt + 1)
-    // and B(kt + 3) refills B stage kt % 3 (over its second group).  The
-    // wait that ends step kt + 1 needs steps kt + 2 complete, so B(kt + 3)
-    // -- the last kNB loads issued -- may still be in flight: each weight
-    // tile has two steps of MFMAs to land, each activation tile one.
-    bf16x8_t a0[MI], b0[NI], a1[MI], b1[NI];
-    DL_READ(0, 0, 0, a0, b0);
-    int sa = 0, sb = 0;
-    int lka = krot(min(1, KT - 1)), lsta = 1;  // A refill in flight (issued by the prologue)
-    int lkb = krot(min(2, KT - 1)), lstb = 2;  // B refill issued by step 0's first group
-    for (int kt = 0; kt < KT; ++kt) {
-      const int nsa = sa ^ 1, nsb = sb == 2 ? 0 : sb + 1;
-      DL_GROUP_R(sa, sb, 1, a1, b1, a0, b0, lka, lsta, lkb, lstb, MI * NI);
-      DL_GROUP(sa, sb, 2, a0, b0, a1, b1);
-      DL_GROUP(sa, sb, 3, a1, b1, a0, b0);
-      wait_vmcnt<kNB>();  // step kt + 1 has landed (this wave's part)
-      __syncthreads();    // ... and every wave's; A stage sa and B stage sb are free
-      lka = krot(min(kt + 2, KT - 1));
-      lsta = sa;
-      lkb = krot(min(kt + 3, KT - 1));
-      lstb = sb;
-      DL_GROUP_R(nsa, nsb, 0, a0, b0, a1, b1, lka, lsta, lkb, lstb, 0);
-      sa = nsa;
-      sb = nsb;
+    for (int i = 0; i < F::kLA; ++i) {
+      const int row = (wave * F::kLA + i) * 8 + (lane >> 3);
+      aoff[u][i] = (uint32_t)(u * 128 + row) * (uint32_t)K * 2u + (uint32_t)(((lane & 7) ^ (lane >> 3)) << 4);
     }
-  } else if constexpr (!FP8 && STAGES == 2) {
-    // The refill of step kt + 2 into stage st starts after the barrier that
-    // ends step kt (in the group computing its last slice) and ends in the
-    // first group of step kt + 1.  That group's first pass repeats half of
-    // the prologue's loads of step 1 (same bytes, same place; they land
-    // before the barrier that ends step 0).
-    bf16x8_t a0[MI], b0[NI], a1[MI], b1[NI];
-    DL_READ(0, 0, 0, a0, b0);
-    int st = 0;
-    int lk = krot(min(1, KT - 1)), lst = 1;  // the refill in flight: its K step and stage
-    for (int kt = 0; kt < KT; ++kt) {
-      const int nst = st ^ 1;
-      DL_GROUP_R(st, st, 1, a1, b1, a0, b0, lk, lst, lk, lst, MI * NI);
-      DL_GROUP(st, st, 2, a0, b0, a1, b1);
-      DL_GROUP(st, st, 3, a1, b1, a0, b0);
-      wait_vmcnt<0>();  // step kt + 1 has landed (this wave's part)
-      __syncthreads();  // ... and every wave's; stage st is free
-      lk = krot(min(kt + STAGES, KT - 1));
-      lst = st;
-      DL_GROUP_R(nst, nst, 0, a0, b0, a1, b1, lk, lst, lk, lst, 0);
-      st = nst;
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int i = 0; i < F::kLB; ++i) {
+      const int lr = wave * 16 + (FP8 ? (lane >> 2) : i * 8 + (lane >> 3));
+      const int c = FP8 ? ((lane & 3) ^ ((lr >> 2) & 3)) : ((lane & 7) ^ (lr & 7));
+      const int col = GATED ? (wave >> 1) * 32 + b * 16 + (lr & 15) : b * 128 + lr;
+      boff[b][i] = (uint32_t)col * (uint32_t)K * (FP8 ? 1u : 2u) + (uint32_t)(c << 4);
     }
-  } else if constexpr (!FP8) {
-    // Deeper rings: the refill of step kt + STAGES into stage st is spread
-    // over the four operand groups of step kt + 1 (it has STAGES - 2 more
-    // steps to land).  The first pass repeats loads of the prologue's last
-    // step (same bytes, same place).
-    bf16x8_t a0[MI], b0[NI], a1[MI], b1[NI];
-    DL_READ(0, 0, 0, a0, b0);
-    int st = 0;
-    int lk = krot(min(STAGES - 1, KT - 1)), lst = STAGES - 1;  // the refill in flight
-    for (int kt = 0; kt < KT; ++kt) {
-      const int nst = st + 1 == STAGES ? 0 : st + 1;
-      DL_GROUP_S(st, 1, a1, b1, a0, b0, lk, lst, MI * NI);
-      DL_GROUP_S(st, 2, a0, b0, a1, b1, lk, lst, 2 * MI * NI);
-      DL_GROUP_S(st, 3, a1, b1, a0, b0, lk, lst, 3 * MI * NI);
-      wait_steps<STAGES - 2, kNB, kPerStep>(per_step);  // step kt + 1 has landed
-      __syncthreads();
-      lk = krot(min(kt + STAGES, KT - 1));
-      lst = st;
-      DL_GROUP_S(nst, 0, a0, b0, a1, b1, lk, lst, 0);
-      st = nst;
-    }
-  } else {
-    bf16x8_t a10[MI], a20[MI], a11[MI], a21[MI], b1[NI], b2[NI];
-    uint4 r0[NI], r1[NI];
-    DL_READ8(0, 0, a10, a20, r0);
-    int st = 0;
-    int lk = krot(min(STAGES - 1, KT - 1)), lst = STAGES - 1;  // the refill in flight
-    for (int kt = 0; kt < KT; ++kt) {
-      const int nst = st + 1 == STAGES ? 0 : st + 1;
-      DL_GROUP8_S(st, 1, a11, a21, r1, a10, a20, r0, lk, lst, 2 * MI * NI);
-      wait_steps<STAGES - 2, kNB, kPerStep>(per_step);  // step kt + 1 has landed
-      __syncthreads();
-      lk = krot(min(kt + STAGES, KT - 1));
-      lst = st;
-      DL_GROUP8_S(nst, 0, a10, a20, r0, a11, a21, r1, lk, lst, 0);
-      st = nst;
-    }
-  }
-#undef DL_GROUP_R
-#undef DL_GROUP_S
-#undef DL_READ1
-#undef DL_GROUP8_S
-#undef DL_READ8_1
-#undef DL_GROUP
-#undef DL_MMA
-#undef DL_WIDEN
-#undef DL_READ8
-#undef DL_READ
-#undef DL_LOAD
+  const uint32_t la = lds_base + wave * (F::kLA * 1024), lb = lds_base + NU * F::kA + wave * (F::kLB * 1024);
 
-  // Split-K: every piece stores its f32 partial sums in its part of the
-  // tile's slot, then counts itself finished; the piece that counts last
-  // adds the parts in piece order -- the same order whichever piece that is,
-  // so results are reproducible run to run -- and runs the epilogue.
-  // Ordering: parts and counter are accessed only with agent-scope atomics,
-  // which the hardware performs at the level that is coherent across the
-  // XCDs' L2 caches; every wave waits for its part stores to be acknowledged
-  // (vmcnt 0) and the workgroup barrier orders that before the counter
-  // increment; the finisher issues its part loads only after the increment
-  // that returned n_split - 1 (the result reaches them through LDS and a
-  // barrier).  So each part is complete at the coherent level before any
-  // load of it is issued.  The atomics are relaxed (no release/acquire
-  // fences): at agent scope those write back and invalidate the whole L2,
-  // which made the pieces slower than no split.
-  if (n_split > 1) {
-    // part layout [wave][fragment][register][lane]: 16 stores 256 bytes apart
-    constexpr int kPart = BM * BN;  // floats
-    float* mine = slot + (int64_t)piece * kPart + wave * (MI * NI * 16 * 64) + lane;
+  Stream st;
+  auto load_a = [&](int u, int stage) {
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+    for (int i = 0; i < F::kLA; ++i)
+      dload16(st.rsA, aoff[u][i], (uint32_t)st.k * 128u, la + stage * F::kStage + u * F::kA + i * 1024);
+  };
+  auto load_b = [&](int b, int stage) {
 #pragma unroll
-      for (int j = 0; j < NI; ++j) {
-        float* dst = mine + (i * NI + j) * (16 * 64);
+    for (int i = 0; i < F::kLB; ++i)
+      dload16(st.rsB, boff[b][i], (uint32_t)st.k * (FP8 ? 64u : 128u), lb + stage * F::kStage + b * F::kB + i * 1024);
+  };
+
+  // operands of one phase, and the accumulators [A unit][B unit][row
+  // fragment][column fragment]: rows of the MFMA result are columns of the
+  // output, so a lane holds four consecutive output columns of one row.
+  // rn: a B unit as read; it becomes rb[b] in widen(b) -- for fp8 weights by
+  // the exact conversion of its bytes, and in family 0 for B unit 0 because
+  // the last phase of a step still multiplies by rb[0] while the next step's
+  // unit is read.
+  bf16x8_t ra[RF][2], rb[2][2][2];
+  uint4 rn[FP8 && FAM != 0 ? 2 : 1][2][FP8 ? 1 : 2];
+  f32x4_t acc[NU][2][RF][2];
+  const int wrow = wm * (F::kUnitRows / 2) + rr;
+  auto read_a = [&](int u, int stage) {
+    const unsigned char* q = smem + stage * F::kStage + u * F::kA + wrow * 128;
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          __hip_atomic_store(dst + r * 64, acc[i][j][r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __builtin_amdgcn_sched_barrier(0);
+    for (int i = 0; i < RF; ++i)
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        // fp8: a lane's 16 weight bytes are 16 consecutive k, so its two
+        // activation chunks are consecutive too
+        const int c = FP8 ? 2 * hh + k : 4 * k + hh;
+        ra[i][k] = *reinterpret_cast<const bf16x8_t*>(q + i * 2048 + ((c ^ (rr & 7)) << 4));
       }
-    wait_vmcnt<0>();  // every store of this wave has completed
-    __syncthreads();  // ... of every wave; the ring is free
-    volatile int* flag = reinterpret_cast<volatile int*>(smem);
-    if (tid == 0)
-      flag[0] = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_split - 1;
-    __syncthreads();
-    const bool last = flag[0] != 0;
-    __syncthreads();  // the flag is read before the epilogue reuses the LDS
-    if (!last) return;
-    if (tid == 0) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next launch
-  }
-
-  // Epilogue: stage bf16 results in LDS ([BM][BN/2 + 8]) and write 16-byte
-  // chunks of whole rows.  Gate/up: one pass, feature fragment j pairs with
-  // up fragment j + NI/2.  Down: two passes of BN/2 columns (each wave
-  // contributes column fragments pass * NI/2 .. pass * NI/2 + NI/2 - 1).
-  // fp8 weights: the per-channel scales multiply the accumulators here.
-  // The loads issued past the last step target the ring this reuses: let
-  // them land first.
-  wait_vmcnt<0>();
-  uint16_t* Cs = reinterpret_cast<uint16_t*>(smem);
-  constexpr int kPasses = GATED ? 1 : 2;
-  constexpr int kChunks = BN / 16;  // 16-byte chunks per staged row
+  };
+  // b = 2: unit 0, kept aside
+  auto read_b = [&](int b, int stage) {
+    const unsigned char* q = smem + stage * F::kStage + NU * F::kA + (b & 1) * F::kB;
 #pragma unroll
-  for (int pass = 0; pass < kPasses; ++pass) {
-    __syncthreads();  // LDS reads of the K loop / previous pass are done
-#pragma unroll
-    for (int jj = 0; jj < NI / 2; ++jj) {
-      const int j = GATED ? jj : pass * (NI / 2) + jj;
-      const int cl = wn * (TN / 2) + jj * 32 + (lane & 31);
-      float sg = 1.f, su = 1.f;
+    for (int j = 0; j < 2; ++j) {
+      const int lr = wn * 32 + j * 16 + rr;
       if constexpr (FP8) {
-        if constexpr (GATED) {
-          const int fc = min(nti * (BN / 2) + cl, n_out - 1);
-          sg = __uint_as_float((uint32_t)wd.s_gu[fc] << 16);
-          su = __uint_as_float((uint32_t)wd.s_gu[n_out + fc] << 16);
-        } else {
-          const int cc = min(nti * BN + wn * TN + j * 32 + (lane & 31), n_out - 1);
-          sg = __uint_as_float((uint32_t)wd.s_down[cc] << 16);
+        rn[FAM == 0 ? 0 : b][j][0] = *reinterpret_cast<const uint4*>(q + lr * 64 + ((hh ^ ((rr >> 2) & 3)) << 4));
+      } else {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const uint4 v = *reinterpret_cast<const uint4*>(q + lr * 128 + (((4 * k + hh) ^ (rr & 7)) << 4));
+          if (b == 2)
+            rn[0][j][k] = v;
+          else
+            rb[b][j][k] = __builtin_bit_cast(bf16x8_t, v);
         }
       }
+    }
+  };
+  auto widen = [&](int b) {
 #pragma unroll
-      for (int i = 0; i < MI; ++i) {
-        // the fragment's values (and its up partner's): the accumulators, or
-        // for a split tile the sum of its pieces' parts in piece order
-        float f0[16], f1[GATED ? 16 : 1];
-        if (n_split > 1) {
-          // every piece's part of the fragment (and of its partner) is
-          // loaded before any is added: one memory round trip, not one per
-          // piece; then the sum in piece order
-          float t0[kMaxSplit][16], t1[kMaxSplit][GATED ? 16 : 1];
-          float* pp = slot + wave * (MI * NI * 16 * 64) + lane + (i * NI + j) * (16 * 64);
+    for (int j = 0; j < 2; ++j) {
+      if constexpr (FP8) {
+        const uint4 v = rn[FAM == 0 ? 0 : b][j][0];
+        const uint2 w0 = e4m3x4_to_bf16x4(v.x), w1 = e4m3x4_to_bf16x4(v.y);
+        const uint2 w2 = e4m3x4_to_bf16x4(v.z), w3 = e4m3x4_to_bf16x4(v.w);
+        rb[b][j][0] = __builtin_bit_cast(bf16x8_t, make_uint4(w0.x, w0.y, w1.x, w1.y));
+        rb[b][j][1] = __builtin_bit_cast(bf16x8_t, make_uint4(w2.x, w2.y, w3.x, w3.y));
+      } else if (FAM == 0 && b == 0) {
 #pragma unroll
-          for (int q = 0; q < kMaxSplit; ++q) {
-            if (q < n_split) {
-              float* p0 = pp + (int64_t)q * (BM * BN);
+        for (int k = 0; k < 2; ++k) rb[0][j][k] = __builtin_bit_cast(bf16x8_t, rn[0][j][k]);
+      }
+    }
+  };
+  auto mma = [&](int u, int b) {
 #pragma unroll
-              for (int r = 0; r < 16; ++r)
-                t0[q][r] = __hip_atomic_load(p0 + r * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              if constexpr (GATED) {
-                float* p1 = p0 + (NI / 2) * (16 * 64);
+    for (int k = 0; k < 2; ++k)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                  t1[q][r] = __hip_atomic_load(p1 + r * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              }
-            }
-          }
+      for (int i = 0; i < RF; ++i)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) f0[r] = 0.f;
+        for (int j = 0; j < 2; ++j)
+          acc[u][b][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rb[b][j][k], ra[i][k], acc[u][b][i][j], 0, 0, 0);
+  };
+
+  Item cur = decode_item<GATED>(p, sc, item, FAM, ncol, KT), nxt = cur;
+  bool split = cur.kn < KT;  // a piece of a tile
+  bool has_next = false;     // the stream has moved on to nxt, item nitem
+  int nitem = -1;
+  stream_set<GATED, FP8, FAM>(st, p, cur, wave);
+
+  __syncthreads();
+  int stage = 0;  // stage of the K step being computed
+  // Loads in flight after the wait of a phase.  Family 0: those of the last
+  // 4 * NST - 2 of its four phases per step; else NST - 2 steps.
+  constexpr int kFlight =
+      FAM == 0 ? (2 * NST - 1) * (F::kLA + F::kLB) : (NST - 2) * (F::kLA + 2 * F::kLB);
+  static_assert(kFlight < 64, "vmcnt range");
+  constexpr int kAhead = FAM == 0 ? NST : NST - 1;  // steps the stream is ahead
+  for (int s = 0; s < kAhead; ++s) {
+    if (st.left == 0) stream_null(st);
+    load_b(0, s);
+    load_a(0, s);
+    load_b(1, s);
+    if constexpr (NU == 2) load_a(1, s);
+    st.next();
+  }
+  if constexpr (FAM == 0) {
+    wait_vmcnt<kFlight>();
+    slot_barrier();
+    read_b(2, 0);
+  } else {
+    wait_vmcnt<kFlight>();
+    slot_barrier();
+  }
+  if (grp == 1) slot_barrier();
+
+  int t = cur.kn;  // K steps of cur still to compute
 #pragma unroll
-          for (int r = 0; r < (GATED ? 16 : 1); ++r) f1[r] = 0.f;
+  for (int u = 0; u < NU; ++u)
 #pragma unroll
-          for (int q = 0; q < kMaxSplit; ++q) {
-            if (q < n_split) {
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-              for (int r = 0; r < 16; ++r) f0[r] += t0[q][r];
-              if constexpr (GATED)
+      for (int i = 0; i < RF; ++i)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) f1[r] += t1[q][r];
-            }
-          }
-        } else {
+        for (int j = 0; j < 2; ++j) acc[u][b][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  for (;;) {
+    if (st.left == 0) {
+      // The stream follows the chain into the next item of the family if this
+      // one is whole and long enough that the stream is at most one item
+      // ahead.
+      const int ni = !has_next && !split && KT > 2 * NST ? round_item(sc, r + 1, nwg, xcd, xj) : -1;
+      if (ni >= 0 && item_family(sc, ni) == FAM) {
+        nxt = decode_item<GATED>(p, sc, ni, FAM, ncol, KT);
+        nitem = ni;
+        has_next = true;
+        stream_set<GATED, FP8, FAM>(st, p, nxt, wave);
+      } else {
+        stream_null(st);
+      }
+    }
+    // steps until the stream or the item ends
+    int seg = min(t, st.left);
+    t -= seg;
+    do {
+      const int ns = stage + 1 == NST ? 0 : stage + 1;
+      if constexpr (FAM == 0) {
+        // Four phases per K step, one per (A unit, B unit) pair, in an order
+        // in which each needs one new operand unit: A0, B1, A1, then B0 of
+        // the next step.  A phase's loads refill the unit that was read one
+        // phase earlier, kAhead steps ahead.
+#define FFN_PHASE(READS, LOADS, WIDEN, MMA) \
+  do {                                      \
+    READS;                                  \
+    LOADS;                                  \
+    wait_vmcnt<kFlight>();                  \
+    wait_lgkm0();                           \
+    WIDEN;                                  \
+    slot_barrier();                         \
+    MMA;                                    \
+    slot_barrier();                         \
+  } while (0)
+        FFN_PHASE(read_a(0, stage), load_b(0, stage), widen(0), mma(0, 0));
+        FFN_PHASE(read_b(1, stage), load_a(0, stage), widen(1), mma(0, 1));
+        FFN_PHASE(read_a(1, stage), load_b(1, stage), (void)0, mma(1, 1));
+        FFN_PHASE(read_b(2, ns), load_a(1, stage); st.next(), (void)0, mma(1, 0));
+#undef FFN_PHASE
+      } else {
+        // One phase per K step; the stage read in the last phase is refilled.
+        const int fs = stage == 0 ? NST - 1 : stage - 1;
+        read_a(0, stage);
+        read_b(0, stage);
+        read_b(1, stage);
+        load_a(0, fs);
+        load_b(0, fs);
+        load_b(1, fs);
+        st.next();
+        wait_vmcnt<kFlight>();
+        wait_lgkm0();
+        widen(0);
+        widen(1);
+        slot_barrier();
+        mma(0, 0);
+        mma(0, 1);
+        slot_barrier();
+      }
+      stage = ns;
+    } while (--seg);
+    if (t > 0) continue;
+
+    constexpr int kPart = F::kRows * kBN;  // floats
+    constexpr int kFrags = NU * 2 * RF * 2;
+    // split tiles: what the finisher adds to its own sums
+    Piece pc{1, 0, 0, 0, 0};
+    unsigned tags = 0;
+    if (split) {
+      pc = decode_piece(sc, item, FAM);
+      // Split tile.  The pieces arrive on the tile's counter word: bits 0-3
+      // count arrivals, bits 4-7 finished parts, bits 8 + 3a the piece that
+      // part a holds.  All but the last arrival store their f32 sums as a
+      // part; the last one waits for the parts (their workgroups have
+      // finished their K steps and only store, so the wait ends) and adds
+      // everything in piece order, so results do not depend on the order of
+      // arrival.  Parts and counter are written and read at agent scope (at
+      // the level that is coherent across the XCDs' L2 caches); a part's
+      // stores have completed (vmcnt 0, barrier) before it is counted, and
+      // the finisher's loads are issued after it has seen the count.
+      if (grp == 0) slot_barrier();  // the groups are in step again
+      wait_vmcnt<0>();
+      slot_barrier();  // the ring is free
+      volatile int* flag = reinterpret_cast<volatile int*>(smem);
+      int32_t* cnt = p.split_cnt + pc.cnt;
+      if (tid == 0)
+        flag[0] = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 15;
+      __syncthreads();
+      const int arrival = __builtin_amdgcn_readfirstlane(flag[0]);
+      if (arrival < pc.n - 1) {
+        __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc(p.split_slots + pc.slot + (int64_t)arrival * kPart, 0, kPart * 4, 0x00020000);
+        const int vo = (wave * kFrags * 64 + lane) * 16;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) f0[r] = acc[i][j][r];
-          if constexpr (GATED)
+        for (int u = 0; u < NU; ++u)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) f1[r] = acc[i][j + NI / 2][r];
+          for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int i = 0; i < RF; ++i)
+#pragma unroll
+              for (int j = 0; j < 2; ++j)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[u][b][i][j]), rs, vo,
+                                                       (((u * 2 + b) * RF + i) * 2 + j) * 1024, 16 /* sc1 */);
+        wait_vmcnt<0>();
+        __syncthreads();  // every wave's part has completed
+        if (tid == 0)
+          __hip_atomic_fetch_add(cnt, 16 + (pc.piece << (8 + 3 * arrival)), __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
+        r += 1;
+        item = round_item(sc, r, nwg, xcd, xj);
+        return;
+      }
+      if (tid == 0) {
+        int w;
+        while ((((w = __hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 4) & 15) < pc.n - 1)
+          __builtin_amdgcn_s_sleep(1);
+        flag[1] = w;
+        __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+      }
+      __syncthreads();
+      tags = (unsigned)uni(flag[1]) >> 8;
+    }
+    // own sums (piece pc.piece) and the parts of the others, in piece order
+    auto add_parts = [&](f32x4_t (&sum)[RF][2], int u, int b) {
+#pragma unroll
+      for (int i = 0; i < RF; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) sum[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      for (int q = 0; q < pc.n; ++q) {
+        if (q == pc.piece) {
+#pragma unroll
+          for (int i = 0; i < RF; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) sum[i][j] += acc[u][b][i][j];
+          continue;
         }
+        int a = 0;  // the part that holds piece q
+        for (int z = 0; z < pc.n - 1; ++z)
+          if ((int)((tags >> (3 * z)) & 7u) == q) a = z;
+        __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            p.split_slots + pc.slot + (int64_t)a * kPart, 0, kPart * 4, 0x00020000);
+        const int vo = (wave * kFrags * 64 + lane) * 16;
+        u32x4_t v[RF][2];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int rl = wm * TM + i * 32 + c_row(lane, r);
-          float v;
+        for (int i = 0; i < RF; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            v[i][j] = __builtin_amdgcn_raw_buffer_load_b128(rs, vo, (((u * 2 + b) * RF + i) * 2 + j) * 1024,
+                                                            16 /* sc1 */);
+#pragma unroll
+        for (int i = 0; i < RF; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) sum[i][j] += __builtin_bit_cast(f32x4_t, v[i][j]);
+      }
+    };
+
+    // Epilogue, from the registers: a lane holds output columns 4hh .. 4hh + 3
+    // of a 16-column fragment for one row; a swap of odd and even 16-lane
+    // rows between two packed fragments gives it 8 consecutive columns, one
+    // 16-byte store.  No LDS, no barrier: the waves go straight on to the
+    // next item, whose first stages the stream has already requested.  Rows
+    // past the group's end are out of the resource's range.
+    {
+      const int rows = min(cur.rows, F::kRows);
+      __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
+          reinterpret_cast<uint16_t*>(p.out) + (int64_t)cur.y_row0 * n_out, 0,
+          (int)((uint32_t)rows * (uint32_t)n_out * 2u), 0x00020000);
+      auto store8 = [&](const uint2 x, const uint2 y, int row, int col) {
+        const auto s0 = __builtin_amdgcn_permlane16_swap(x.x, y.x, false, false);
+        const auto s1 = __builtin_amdgcn_permlane16_swap(x.y, y.y, false, false);
+        const u32x4_t v = {(unsigned)s0[0], (unsigned)s1[0], (unsigned)s0[1], (unsigned)s1[1]};
+        const uint32_t off = ((uint32_t)row * (uint32_t)n_out + (uint32_t)col) * 2u;
+        __builtin_amdgcn_raw_buffer_store_b128(v, ro, row < rows && col < n_out ? off : 0xfffffff0u, 0, 0);
+      };
+      auto pack = [](float a, float b) {
+        bf16x2v_t v;
+        v[0] = (__bf16)a;
+        v[1] = (__bf16)b;
+        return __builtin_bit_cast(uint32_t, v);
+      };
+      const WeightDesc& wd = p.wtab[cur.g];
+      // four bf16 scales from column c on
+      auto scales = [&](const uint16_t* s, int c) {
+        uint2 v;  // the caller's scales are 2-byte aligned
+        __builtin_memcpy(&v, s + min(c, n_out - 4), 8);
+        return f32x4_t{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
+                       __uint_as_float(v.y & 0xffff0000u)};
+      };
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        f32x4_t sg, su;
+        if constexpr (FP8) {
           if constexpr (GATED) {
-            const float gv = FP8 ? f0[r] * sg : f0[r];
-            const float uv = FP8 ? f1[r] * su : f1[r];
-            v = gv * __builtin_amdgcn_rcpf(1.f + __expf(-gv)) * uv;
+            const int c = cur.nti * (kBN / 2) + wn * 32 + b * 16 + hh * 4;
+            sg = scales(wd.s_gu, c);
+            // the up scales start at element n_out, a multiple of 64
+            su = scales(wd.s_gu + n_out, c);
           } else {
-            v = FP8 ? f0[r] * sg : f0[r];
+            const int c = cur.nti * kBN + b * 128 + wn * 32 + hh * 4;
+            sg = scales(wd.s_down, c);
+            su = scales(wd.s_down, c + 16);
           }
-          Cs[rl * kLd + cl] = (uint16_t)f32_to_bf16_rne(v);
+        }
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+          const int row0 = u * 128 + wm * (F::kUnitRows / 2) + rr;
+          f32x4_t o[RF][2];
+          if (split) {
+            add_parts(o, u, b);
+          } else {
+#pragma unroll
+            for (int i = 0; i < RF; ++i)
+#pragma unroll
+              for (int j = 0; j < 2; ++j) o[i][j] = acc[u][b][i][j];
+          }
+          if constexpr (GATED) {
+            const int col = cur.nti * (kBN / 2) + wn * 32 + b * 16 + (hh >> 1) * 8;
+#pragma unroll
+            for (int i = 0; i < RF; i += 2) {
+              uint2 w[2];
+#pragma unroll
+              for (int q = 0; q < 2; ++q) {
+                float v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                  float gv = o[i + q][0][e], uv = o[i + q][1][e];
+                  if constexpr (FP8) {
+                    gv *= sg[e];
+                    uv *= su[e];
+                  }
+                  v[e] = gv * __builtin_amdgcn_rcpf(1.f + __expf(-gv)) * uv;
+                }
+                w[q] = make_uint2(pack(v[0], v[1]), pack(v[2], v[3]));
+              }
+              store8(w[0], w[1], row0 + (i + (hh & 1)) * 16, col);
+            }
+          } else {
+            const int col = cur.nti * kBN + b * 128 + wn * 32 + (hh & 1) * 16 + (hh >> 1) * 8;
+#pragma unroll
+            for (int i = 0; i < RF; ++i) {
+              uint2 w[2];
+#pragma unroll
+              for (int j = 0; j < 2; ++j) {
+                f32x4_t v = o[i][j];
+                if constexpr (FP8) v *= j == 0 ? sg : su;
+                w[j] = make_uint2(pack(v[0], v[1]), pack(v[2], v[3]));
+              }
+              store8(w[0], w[1], row0 + i * 16, col);
+            }
+          }
         }
       }
     }
-    __syncthreads();
-#pragma unroll 4
-    for (int it = 0; it < BM * kChunks / 256; ++it) {
-      const int q = tid + 256 * it;
-      const int rl = q / kChunks, cc = q % kChunks;
-      const int row = m0 + rl;
-      const int sc = cc * 8;  // staged column
-      const int col = GATED ? nti * (BN / 2) + sc
-                            : nti * BN + (sc / (TN / 2)) * TN + pass * (TN / 2) + sc % (TN / 2);
-      if (row < gd.n && col < n_out) {
-        const uint4 v = *reinterpret_cast<const uint4*>(&Cs[rl * kLd + sc]);
-        *reinterpret_cast<uint4*>(O + (int64_t)(gd.y_row0 + row) * n_out + col) = v;
+
+    r += 1;
+    if (!has_next) {
+      item = round_item(sc, r, nwg, xcd, xj);
+      if (!split) {
+        if (grp == 0) slot_barrier();  // the groups are in step again
+        wait_vmcnt<0>();               // no load still targets the ring
       }
+      return;
     }
+    item = nitem;
+    cur = nxt;
+    split = cur.kn < KT;
+    has_next = false;
+    t = cur.kn;
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int i = 0; i < RF; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[u][b][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
 }
 
-// The FFN launch for bf16 or fp8 weights: every tile of the big family (256
-// rows), then the medium (128 rows; 256 for a cold expert's remainder above
-// 128 rows) and small (64 rows) tiles of the row remainders and of cold
-// experts, in one persistent grid.  The smaller families come last, so they
-// also fill the tail of the big one; cold
-// experts are weight-streaming bound, and narrow tiles spread each expert's
-// weights over more CUs.  bf16 big tiles keep 2 activation stages and 3
-// weight stages (all 160 KB of LDS; the plan's tile -> group map replaces a
-// group table in LDS).  fp8 stages are smaller (e4m3 B tiles), so their
-// rings are deeper: 3 big / 6 medium and small stages instead of 2 / 4.
-template <bool FP8>
-constexpr int ring_bytes(int a_stages, int b_stages, int bm, int bn) {
-  return a_stages * bm * kBK * 2 + b_stages * bn * kBK * (FP8 ? 1 : 2);
-}
-constexpr int cmax(int a, int b) { return a > b ? a : b; }
+// The FFN launch for bf16 or fp8 weights.
 template <bool GATED, bool FP8>
-__global__ __launch_bounds__(256, 1) void ffn_dlds_kernel(const FfnParams p) {
-  // fp8 small tiles are twice as wide: per K step they read as many weight
-  // bytes as bf16 ones and half the activation bytes per weight byte
-  constexpr int kSBN = FP8 ? kSmallBN8 : kSmallBN;
-  constexpr int kBigStages = FP8 ? 3 : 2, kBigBStages = FP8 ? 3 : 3, kSmallStages = FP8 ? 6 : 4,
-                kTallStages = 3;
-  constexpr int kRing = cmax(cmax(ring_bytes<FP8>(kBigStages, kBigBStages, kBM, kBN),
-                                  ring_bytes<FP8>(kTallStages, kTallStages, kTallBM, kMedBN)),
-                             cmax(ring_bytes<FP8>(kSmallStages, kSmallStages, kMedBM, kMedBN),
-                                  ring_bytes<FP8>(kSmallStages, kSmallStages, kSmallBM, kSBN)));
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[kRing];
+__global__ __launch_bounds__(512, 2) void ffn_mfma_kernel(const FfnParams p) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kFfnLds];
   const bool probe = p.clk != nullptr && (int)blockIdx.x < p.clk_n;
   unsigned long long clk0 = 0, rt0 = 0;
   if (probe) {
     clk0 = __builtin_amdgcn_s_memtime();
     rt0 = __builtin_amdgcn_s_memrealtime();
   }
-  const int stage = GATED ? 0 : 1, st3 = 3 * stage;
-  const int tot0 = p.tile_totals[st3], tot1 = p.tile_totals[st3 + 1], tot2 = p.tile_totals[st3 + 2];
   const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_vptr)smem;
   const int nwg = gridDim.x;
-  const int ncol_big = GATED ? (p.n_out + kBN / 2 - 1) / (kBN / 2) : (p.n_out + kBN - 1) / kBN;
-  // The weight-streaming families (medium, tall, small) rotate their K walk
-  // by tile; big tiles share activation and weight bands with the tiles next
-  // to them in an XCD's L2, which a rotation would pull apart.
-  constexpr bool kRotateBig = false;
-  const int total = tot0 + tot1 + tot2;
-  // Split-K: a launch of at most half a grid of tiles cuts each tile into
-  // n_split pieces of consecutive K steps (at least kMinSplitSteps each), so
-  // that more CUs stream its weights; the partial sums of a tile's pieces
-  // take n_split parts of its slot (big tiles first, then family 1, then
-  // small, each slot sized for its family).
-  int n_split = 1;
-  int64_t slot1 = 0, slot2 = 0;  // float offsets of the family 1 and small slots
-  if (p.split_slots != nullptr && total > 0 && 2 * total <= nwg && total <= kSplitCounters) {
-    n_split = max(1, min(min(kMaxSplit, nwg / total), p.K / (kBK * kMinSplitSteps)));
-    const int64_t per = (int64_t)tot0 * (kBM * kBN) + (int64_t)tot1 * (kTallBM * kMedBN) +
-                        (int64_t)tot2 * (kSmallBM * kSBN);  // floats per piece
-    while (n_split > 1 && (int64_t)n_split * per * 4 > p.split_bytes) --n_split;
-    slot1 = (int64_t)n_split * tot0 * (kBM * kBN);
-    slot2 = slot1 + (int64_t)n_split * tot1 * (kTallBM * kMedBN);
-  }
-  const int items = total * n_split;  // work item = tile * n_split + piece
-  // Work items go round by round: a full round of the grid gives each XCD
-  // (the hardware deals workgroups round robin over the 8 XCDs) a run of
-  // nwg / 8 consecutive items; a partial round gives each XCD a run of
-  // ceil(count / 8), so a launch with fewer items than workgroups still
-  // uses every XCD's L2 and memory path.
   const int xcd = blockIdx.x & 7, xj = blockIdx.x >> 3;
-  for (int base = 0; base < items; base += nwg) {
-    const int cnt = min(nwg, items - base);
-    const int q = cnt == nwg ? (nwg >> 3) : ((cnt + 7) >> 3);
-    const int idx = xcd * q + xj;
-    if (xj >= q || idx >= cnt) continue;
-    const int item = base + idx;
-    const int tile = item / n_split, piece = item - tile * n_split;
-    const int g = p.tile_group[tile];
-    const GroupDesc gd = p.groups[g];
-    if (tile < tot0) {
-      const int local = tile - gd.t0[st3];
-      int rt, nti;
-      panel_decode<GATED ? 8 : 4>(local, gd.nrt[stage][0], ncol_big, rt, nti);
-      dl_tile<GATED, FP8, kBM, kBN, kBigStages, kBigBStages, kRing>(
-          p, smem, lds_base, gd, p.wtab[g], nti, rt * kBM, kRotateBig ? tile : -1, n_split, piece,
-          n_split > 1 ? p.split_slots + (int64_t)tile * n_split * (kBM * kBN) : nullptr, p.split_cnt + tile);
-    } else {
-      // medium or small: the row tiles of one column tile are consecutive
-      const bool med = tile < tot0 + tot1;
-      const int f = med ? 1 : 2;
-      const int local = tile - (med ? tot0 : tot0 + tot1) - gd.t0[st3 + f];
-      const int nti = local / gd.nrt[stage][f];
-      const int ri = local - nti * gd.nrt[stage][f];
-      float* sl = n_split == 1 ? nullptr
-                  : med ? p.split_slots + slot1 + (int64_t)(tile - tot0) * n_split * (kTallBM * kMedBN)
-                        : p.split_slots + slot2 + (int64_t)(tile - tot0 - tot1) * n_split * (kSmallBM * kSBN);
-      if (med && gd.h1[stage] == kTallBM)
-        dl_tile<GATED, FP8, kTallBM, kMedBN, kTallStages, kTallStages, kRing>(
-            p, smem, lds_base, gd, p.wtab[g], nti, gd.row1[stage] + ri * kTallBM, tile, n_split, piece, sl,
-            p.split_cnt + tile);
-      else if (med)
-        dl_tile<GATED, FP8, kMedBM, kMedBN, kSmallStages, kSmallStages, kRing>(
-            p, smem, lds_base, gd, p.wtab[g], nti, gd.row1[stage] + ri * kMedBM, tile, n_split, piece, sl,
-            p.split_cnt + tile);
-      else
-        dl_tile<GATED, FP8, kSmallBM, kSBN, kSmallStages, kSmallStages, kRing>(
-            p, smem, lds_base, gd, p.wtab[g], nti, gd.row2[stage] + ri * kSmallBM, tile, n_split, piece, sl,
-            p.split_cnt + tile);
-    }
+  Sched sc;
+  make_sched(sc, p, p.tile_totals + (GATED ? 0 : 3), nwg, p.K / kBK, reinterpret_cast<int*>(smem));
+  int r = 0;
+  int item = round_item(sc, r, nwg, xcd, xj);
+  while (item >= 0) {
+    const int f = item_family(sc, item);
+    if (f == 0)
+      run_family<GATED, FP8, 0>(p, sc, smem, lds_base, nwg, xcd, xj, r, item);
+    else if (f == 1)
+      run_family<GATED, FP8, 1>(p, sc, smem, lds_base, nwg, xcd, xj, r, item);
+    else
+      run_family<GATED, FP8, 2>(p, sc, smem, lds_base, nwg, xcd, xj, r, item);
   }
   if (probe) {
     const unsigned long long clk1 = __builtin_amdgcn_s_memtime(), rt1 = __builtin_amdgcn_s_memrealtime();
@@ -889,8 +863,8 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const FfnParams p) {
     const GroupDesc gd = p.groups[g];
     const WeightDesc wd = p.wtab[g];
     const int local = tile - gd.t0[GATED ? 0 : 3];
-    const int nti = local / gd.nrt[GATED ? 0 : 1][0];
-    const int m0 = (local - nti * gd.nrt[GATED ? 0 : 1][0]) * BM;
+    const int nti = local / gd.nrt[0];
+    const int m0 = (local - nti * gd.nrt[0]) * BM;
     const int arow0 = GATED ? gd.x_row0 : gd.y_row0;
     const int lr = tid >> 2, lk = (tid & 3) * 4;
     const float* asrc = A + (int64_t)(arow0 + min(m0 + lr, gd.n - 1)) * K + lk;
@@ -984,17 +958,19 @@ hipError_t launch_ffn(int stage, int act_dtype, int w_dtype, const GroupDesc* gr
       ffn_f32_kernel<false><<<grid, 256, 0, s>>>(p);
     return hipGetLastError();
   }
-  const int grid = grid_for(max_tiles, num_cu);  // one 256-thread workgroup per CU (LDS, registers)
+  // one 512-thread workgroup per CU; the tail of a launch is cut to fill the
+  // whole grid, however few its tiles
+  const int grid = grid_for(num_cu, num_cu);
   if (w_dtype == 2) {
     if (stage == 0)
-      ffn_dlds_kernel<true, true><<<grid, 256, 0, s>>>(p);
+      ffn_mfma_kernel<true, true><<<grid, 512, 0, s>>>(p);
     else
-      ffn_dlds_kernel<false, true><<<grid, 256, 0, s>>>(p);
+      ffn_mfma_kernel<false, true><<<grid, 512, 0, s>>>(p);
   } else {
     if (stage == 0)
-      ffn_dlds_kernel<true, false><<<grid, 256, 0, s>>>(p);
+      ffn_mfma_kernel<true, false><<<grid, 512, 0, s>>>(p);
     else
-      ffn_dlds_kernel<false, false><<<grid, 256, 0, s>>>(p);
+      ffn_mfma_kernel<false, false><<<grid, 512, 0, s>>>(p);
   }
   return hipGetLastError();
 }

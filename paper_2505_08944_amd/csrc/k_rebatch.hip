@@ -21,10 +21,6 @@
 
 namespace aep {
 
-struct NT6 {
-  int v[6];
-};
-
 constexpr int kPlanThreads = 1024;
 
 // Exclusive scan of NV ints per thread over a workgroup of kPlanThreads
@@ -79,92 +75,47 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(int E, int S, int n_
                                                             int32_t* __restrict__ offsets,
                                                             GroupDesc* __restrict__ groups,
                                                             int32_t* __restrict__ tile_totals,
-                                                            NT6 nt, int big_bm, int med_bm, int small_bm,
-                                                            int num_cu,
+                                                            int nt0, int nt1, int bm, int families,
                                                             int32_t* __restrict__ tile_group,
                                                             int64_t tile_cap,
                                                             int32_t* __restrict__ pos,
                                                             float* __restrict__ posw) {
   const int tid = threadIdx.x;
   if (blockIdx.x == 0) {
-    __shared__ int32_t wsum4[kPlanThreads / 64 + 1][4];
     __shared__ int32_t wsum7[kPlanThreads / 64 + 1][7];
     const int G = E + S;
     const int g = tid;
     const bool real = g < G;
     const int n = !real ? 0 : g < E ? (only_expert < 0 || g == only_expert ? depth[g] : 0) : n_tokens;
-    const int full = n / big_bm, r = n - full * big_bm;
-    // routed rows; full big gate/up tiles of the whole batch; big row tiles
-    // when a remainder above 3/4 of a big tile takes one more (rule A) and
-    // when any remainder above one medium tile does (rule B)
-    int a[4] = {g < E ? n : 0, full * nt.v[0], full + (r > big_bm - big_bm / 4 ? 1 : 0),
-                full + (r > med_bm ? 1 : 0)};
-    int sum4[4];
-    plan_block_scan<4>(a, sum4, wsum4);
-    const int N = sum4[0];
-    // A batch whose full big tiles do not fill one round of the grid is
-    // cold: its remainders go to medium tiles only (a few long big tiles
-    // would be the critical path of a weight-streaming launch).
-    const bool cold = sum4[1] < num_cu;
-    int nrt[2][3] = {{0, 0, 0}, {0, 0, 0}};
-    int fam1_rows[2] = {0, 0};   // rows covered by family 1 before the small tile
-    int h1[2] = {med_bm, med_bm};  // rows per family-1 tile
-#pragma unroll
-    for (int st = 0; st < 2; ++st) {
-      // Rule B trades the medium and small tiles of a remainder (each
-      // streams the expert's weights again, and their per-tile overheads
-      // weigh more) for one big tile with idle rows; it is taken unless its
-      // extra big tiles start another round of the grid in a stage that has
-      // few rounds (there a round of long big tiles would run nearly alone).
-      const int ntb = nt.v[3 * st];
-      const int rounds_a = (sum4[2] * ntb + num_cu - 1) / num_cu;
-      const int rounds_b = (sum4[3] * ntb + num_cu - 1) / num_cu;
-      const int xbig = rounds_b == rounds_a || rounds_a >= 4 ? med_bm : big_bm - big_bm / 4;
-      if (small_bm == 0) {
-        nrt[st][0] = (n + big_bm - 1) / big_bm;
-      } else if (cold && r > med_bm) {
-        // full big tiles; a remainder above one medium tile takes one tall
-        // tile (kTallBM rows: the expert's weights are read once)
-        nrt[st][0] = full;
-        nrt[st][1] = 1;
-        h1[st] = kTallBM;
-      } else if (r > xbig) {
-        nrt[st][0] = full + 1;
-      } else {
-        // full big tiles, then full medium tiles; what is left goes to one
-        // more medium tile above small_bm rows, else to one small tile
-        nrt[st][0] = full;
-        nrt[st][1] = r / med_bm;
-        const int rem = r - nrt[st][1] * med_bm;
-        if (rem > small_bm)
-          nrt[st][1] += 1;
-        else if (rem > 0)
-          nrt[st][2] = 1;
-        fam1_rows[st] = (r / med_bm) * med_bm;
-      }
-    }
+    // full blocks, and the remainder in one tile of the smallest family that
+    // holds it
+    const int full = n / bm, rem = n - full * bm;
+    int nrt[3] = {full, 0, 0};
+    if (families == 1 || rem > bm / 2)
+      nrt[0] += rem > 0 ? 1 : 0;
+    else if (rem > bm / 4)
+      nrt[1] = 1;
+    else if (rem > 0)
+      nrt[2] = 1;
     int b[7];
     b[0] = n;
 #pragma unroll
-    for (int i = 0; i < 6; ++i) b[1 + i] = nrt[i / 3][i % 3] * nt.v[i];
+    for (int i = 0; i < 6; ++i) b[1 + i] = nrt[i % 3] * (i < 3 ? nt0 : nt1);
     int sum7[7];
     plan_block_scan<7>(b, sum7, wsum7);
     if (real) {
       GroupDesc gd;
       gd.n = n;
-      gd.x_row0 = g < E ? b[0] : N;
+      // shared groups all read the token rows that follow the routed ones
+      gd.x_row0 = b[0];
       gd.y_row0 = b[0];
 #pragma unroll
       for (int i = 0; i < 6; ++i) gd.t0[i] = b[1 + i];
 #pragma unroll
-      for (int st = 0; st < 2; ++st) {
-#pragma unroll
-        for (int f = 0; f < 3; ++f) gd.nrt[st][f] = nrt[st][f];
-        gd.row1[st] = full * big_bm;
-        gd.row2[st] = full * big_bm + fam1_rows[st];
-        gd.h1[st] = h1[st];
-      }
+      for (int f = 0; f < 3; ++f) gd.nrt[f] = nrt[f];
+      gd.row1 = full * bm;
       gd.pad[0] = gd.pad[1] = gd.pad[2] = 0;
+      if (g >= E) gd.x_row0 = b[0] - (g - E) * n_tokens;
       groups[g] = gd;
       counts[g] = n;
       offsets[g] = b[0];
@@ -175,7 +126,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(int E, int S, int n_
       for (int i = 0; i < 6; ++i) tile_totals[i] = sum7[1 + i];
     }
     // The group of every tile of both launches (tiles are numbered per
-    // launch: the big family, then the medium, then the small): the last
+    // launch, family by family): the last
     // group whose first tile in that family is not above the tile.
     __shared__ int32_t t0s[6][kMaxGroups + 1];
     if (real)
@@ -278,16 +229,13 @@ __global__ __launch_bounds__(256) void gather_kernel(
 
 hipError_t launch_plan(int E, int S, int n_tokens, int k, int only_expert, int32_t* depth,
                        int32_t* depth_other, int32_t* counts, int32_t* offsets, GroupDesc* groups,
-                       int32_t* tile_totals, const int* nt, int big_bm, int med_bm, int small_bm,
-                       int num_cu, int32_t* tile_group, int64_t tile_cap, int32_t* pos, float* posw,
+                       int32_t* tile_totals, const int* nt, int bm, int families, int32_t* tile_group, int64_t tile_cap, int32_t* pos, float* posw,
                        hipStream_t s) {
-  NT6 n6;
-  for (int i = 0; i < 6; ++i) n6.v[i] = nt[i];
   static_assert(kMaxGroups <= kPlanThreads, "one plan thread per group");
   const int64_t nk = (int64_t)n_tokens * k;
   const unsigned nb = (unsigned)std::min<int64_t>(256, std::max<int64_t>(1, (nk + 4 * kPlanThreads - 1) / (4 * kPlanThreads)));
   plan_kernel<<<nb, kPlanThreads, 0, s>>>(E, S, n_tokens, k, only_expert, depth, depth_other, counts, offsets, groups,
-                                  tile_totals, n6, big_bm, med_bm, small_bm, num_cu, tile_group, tile_cap,
+                                  tile_totals, nt[0], nt[1], bm, families, tile_group, tile_cap,
                                   pos, posw);
   return hipGetLastError();
 }
