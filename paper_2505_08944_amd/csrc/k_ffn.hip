@@ -62,17 +62,30 @@ typedef __attribute__((address_space(3))) void* lds_vptr;
 
 // A raw buffer resource over [base, base + bytes): stride 0, 32-bit data
 // format, every access bounds-checked against bytes (an access past the end
-// reads zeros without touching memory and writes nothing).  The fields are
-// uniform (SGPRs).
+// reads zeros without touching memory and writes nothing).  Its words are
+// kept apart, as scalars, and only put together where a load uses them: as
+// one four-word value that is changed word by word (null below) across the
+// branches of a chain, the compiler let a branch keep stale words.
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ i32x4_t make_rsrc(const void* base, uint32_t bytes) {
+struct Rsrc {
+  int lo, hi, bytes;
+  __device__ __forceinline__ i32x4_t words() const { return i32x4_t{lo, hi, bytes, 0x00020000 /* data format 32 */}; }
+};
+__device__ __forceinline__ Rsrc make_rsrc(const void* base, uint32_t bytes) {
   const uint64_t a = (uint64_t)(uintptr_t)base;
-  i32x4_t r;
-  r.x = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
-  r.y = __builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xFFFFu));
-  r.z = __builtin_amdgcn_readfirstlane((int)bytes);
-  r.w = 0x00020000;  // data format 32
-  return r;
+  return Rsrc{__builtin_amdgcn_readfirstlane((int)(uint32_t)a),
+              __builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xFFFFu)),
+              __builtin_amdgcn_readfirstlane((int)bytes)};
+}
+
+// Tables of earlier launches (plan, weights), read through the scalar cache:
+// a vector load would be waited for together with every direct-to-LDS load in
+// flight, which drains the operand ring at each tile (vmcnt counts both).
+template <typename T>
+using const_ptr = const __attribute__((address_space(4))) T*;
+template <typename T>
+__device__ __forceinline__ const_ptr<T> as_const(const T* p) {
+  return (const_ptr<T>)(uintptr_t)p;
 }
 
 // One direct buffer -> LDS load: lane l reads the 16 bytes at byte offset
@@ -82,7 +95,8 @@ __device__ __forceinline__ i32x4_t make_rsrc(const void* base, uint32_t bytes) {
 // outstanding load before each LDS read); the kernel orders these loads
 // itself with wait_vmcnt + barriers.
 __device__ __forceinline__ void dload16(i32x4_t rsrc, uint32_t voff, uint32_t soff, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %3\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(rsrc),
+  // (one wait state between the write of M0 and its use)
+  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(rsrc),
                "s"(soff), "s"(__builtin_amdgcn_readfirstlane(lds_addr))
                : "memory", "m0");
 }
@@ -136,6 +150,8 @@ __device__ __forceinline__ void panel_decode(int local, int nrow, int ncol, int&
 struct Sched {
   int b1, b2, total;  // first tile of families 1 and 2, and the number of tiles
   int whole, items;
+  int full;           // full rounds of items
+  bool mixed;         // 256-row tiles beside a sixth as many smaller ones or more
   int nsp;            // pieces per tail tile: family f in bits 4f .. 4f + 3
   __device__ __forceinline__ int first(int f) const { return f == 0 ? 0 : f == 1 ? b1 : f == 2 ? b2 : total; }
   // first tail tile of family f and how many there are
@@ -178,10 +194,22 @@ __device__ __forceinline__ int round_item(const Sched& s, int r, int nwg, int xc
   return xj < q && idx < cnt ? base + idx : -1;
 }
 
+// The r-th item of workgroup slot (xcd, xj); -1 past its last one.  In a
+// mixed launch odd XCDs take their rounds from the last to the first: the
+// 256-row tiles, which come first, are bound by the matrix cores and the
+// smaller ones by HBM, so the two kinds run side by side instead of one after
+// the other (1999 tokens of the fine-grained layer: -4%; all but pure launches
+// of large tiles, which share weight bands between the XCDs: +2%).
+__device__ __forceinline__ int nth_item(const Sched& s, int r, int nwg, int xcd, int xj) {
+  if (!(xcd & 1) || !s.mixed) return round_item(s, r, nwg, xcd, xj);
+  const int nr = s.full + (round_item(s, s.full, nwg, xcd, xj) >= 0 ? 1 : 0);
+  return r < nr ? round_item(s, nr - 1 - r, nwg, xcd, xj) : -1;
+}
+
 // Pieces per tail tile: every combination of up to kMaxSplit pieces per
 // family is tried by one thread, which adds up the loads of a sample of
 // workgroups; the smallest maximum wins (fewest pieces on a tie).
-__device__ __forceinline__ void make_sched(Sched& s, const FfnParams& p, const int32_t* tot, int nwg, int KT,
+__device__ __forceinline__ void make_sched(Sched& s, const FfnParams& p, const_ptr<int32_t> tot, int nwg, int KT,
                                            int* lds) {
   const int tid = threadIdx.x;
   s.b1 = uni(tot[0]);
@@ -281,18 +309,18 @@ __device__ __forceinline__ Item decode_item(const FfnParams& p, const Sched& s, 
   Item it;
   it.k0 = q.n == 1 ? 0 : uni(q.piece * KT / q.n);
   it.kn = q.n == 1 ? KT : uni((q.piece + 1) * KT / q.n) - it.k0;
-  it.g = uni(p.tile_group[q.tile]);
-  const GroupDesc& gd = p.groups[it.g];
-  const int local = q.tile - s.first(f) - gd.t0[(GATED ? 0 : 3) + f];
+  it.g = uni(as_const(p.tile_group)[q.tile]);
+  const const_ptr<GroupDesc> gd = as_const(p.groups) + it.g;
+  const int local = q.tile - s.first(f) - gd->t0[(GATED ? 0 : 3) + f];
   int m0;
   if (f == 0) {
     int rt;
-    panel_decode<GATED ? 8 : 4>(local, gd.nrt[0], ncol, rt, it.nti);
+    panel_decode<GATED ? 8 : 4>(local, gd->nrt[0], ncol, rt, it.nti);
     m0 = rt * kBM;
     it.rot = 0;
   } else {
     it.nti = local;
-    m0 = gd.row1;
+    m0 = gd->row1;
     // Smaller tiles stream weights: tiles that run together start their K
     // walk at different steps, so they do not read the same DRAM channels
     // in lockstep (a load-only probe: 0.68 -> 0.79 of peak bandwidth).
@@ -300,9 +328,9 @@ __device__ __forceinline__ Item decode_item(const FfnParams& p, const Sched& s, 
     // a rotation would pull apart.
     it.rot = uni((int)((7u * (unsigned)q.tile) % (unsigned)it.kn));
   }
-  it.rows = uni(gd.n - m0);
-  it.x_row0 = uni(gd.x_row0 + m0);
-  it.y_row0 = uni(gd.y_row0 + m0);
+  it.rows = uni(gd->n - m0);
+  it.x_row0 = uni(gd->x_row0 + m0);
+  it.y_row0 = uni(gd->y_row0 + m0);
   it.nti = uni(it.nti);
   return it;
 }
@@ -335,7 +363,7 @@ struct Fam {
 // The load stream: which item's which K step the next stage is filled from.
 // It runs kStages steps ahead of the MFMAs, across items.
 struct Stream {
-  i32x4_t rsA, rsB;
+  Rsrc a, b;
   int k, k0, kend, left;
   __device__ __forceinline__ void next() {
     --left;
@@ -346,17 +374,17 @@ struct Stream {
 template <bool GATED, bool FP8, int FAM>
 __device__ __forceinline__ void stream_set(Stream& st, const FfnParams& p, const Item& it, int wave) {
   const int K = p.K;
-  const WeightDesc& wd = p.wtab[it.g];
+  const const_ptr<WeightDesc> wd = as_const(p.wtab) + it.g;
   const uint16_t* a = reinterpret_cast<const uint16_t*>(p.a) + (int64_t)(GATED ? it.x_row0 : it.y_row0) * K;
   // rows past the group's end and columns past the matrix are out of the
   // resources' range: they read as zeros, cost no traffic, and their outputs
   // are not stored
-  st.rsA = make_rsrc(a, (uint32_t)min(it.rows, Fam<FP8, FAM>::kRows) * (uint32_t)K * 2u);
+  st.a = make_rsrc(a, (uint32_t)min(it.rows, Fam<FP8, FAM>::kRows) * (uint32_t)K * 2u);
   const unsigned char* w =
-      reinterpret_cast<const unsigned char*>(GATED ? ((wave & 1) ? wd.up : wd.gate) : wd.down);
+      reinterpret_cast<const unsigned char*>(GATED ? ((wave & 1) ? wd->up : wd->gate) : wd->down);
   const int c0 = it.nti * (GATED ? kBN / 2 : kBN);
   constexpr uint32_t esz = FP8 ? 1u : 2u;
-  st.rsB = make_rsrc(w + (int64_t)c0 * K * esz, (uint32_t)(p.n_out - c0) * (uint32_t)K * esz);
+  st.b = make_rsrc(w + (int64_t)c0 * K * esz, (uint32_t)(p.n_out - c0) * (uint32_t)K * esz);
   st.k0 = it.k0;
   st.kend = it.k0 + it.kn;
   st.k = it.k0 + it.rot;
@@ -364,7 +392,8 @@ __device__ __forceinline__ void stream_set(Stream& st, const FfnParams& p, const
 }
 __device__ __forceinline__ void stream_null(Stream& st) {
   // every lane is out of range (the scalar offset stays 0): no traffic
-  st.rsA.z = st.rsB.z = 0;
+  st.a.bytes = 0;
+  st.b.bytes = 0;
   st.k = st.k0 = 0;
   st.kend = 1;
   st.left = INT_MAX;
@@ -412,12 +441,12 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
   auto load_a = [&](int u, int stage) {
 #pragma unroll
     for (int i = 0; i < F::kLA; ++i)
-      dload16(st.rsA, aoff[u][i], (uint32_t)st.k * 128u, la + stage * F::kStage + u * F::kA + i * 1024);
+      dload16(st.a.words(), aoff[u][i], (uint32_t)st.k * 128u, la + stage * F::kStage + u * F::kA + i * 1024);
   };
   auto load_b = [&](int b, int stage) {
 #pragma unroll
     for (int i = 0; i < F::kLB; ++i)
-      dload16(st.rsB, boff[b][i], (uint32_t)st.k * (FP8 ? 64u : 128u), lb + stage * F::kStage + b * F::kB + i * 1024);
+      dload16(st.b.words(), boff[b][i], (uint32_t)st.k * (FP8 ? 64u : 128u), lb + stage * F::kStage + b * F::kB + i * 1024);
   };
 
   // operands of one phase, and the accumulators [A unit][B unit][row
@@ -535,7 +564,7 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
       // The stream follows the chain into the next item of the family if this
       // one is whole and long enough that the stream is at most one item
       // ahead.
-      const int ni = !has_next && !split && KT > 2 * NST ? round_item(sc, r + 1, nwg, xcd, xj) : -1;
+      const int ni = !has_next && !split && KT > 2 * NST ? nth_item(sc, r + 1, nwg, xcd, xj) : -1;
       if (ni >= 0 && item_family(sc, ni) == FAM) {
         nxt = decode_item<GATED>(p, sc, ni, FAM, ncol, KT);
         nitem = ni;
@@ -614,7 +643,8 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
       if (grp == 0) slot_barrier();  // the groups are in step again
       wait_vmcnt<0>();
       slot_barrier();  // the ring is free
-      volatile int* flag = reinterpret_cast<volatile int*>(smem);
+      volatile __attribute__((address_space(3))) int* flag =
+          (volatile __attribute__((address_space(3))) int*)smem;
       int32_t* cnt = p.split_cnt + pc.cnt;
       if (tid == 0)
         flag[0] = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 15;
@@ -640,7 +670,7 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
           __hip_atomic_fetch_add(cnt, 16 + (pc.piece << (8 + 3 * arrival)), __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_AGENT);
         r += 1;
-        item = round_item(sc, r, nwg, xcd, xj);
+        item = nth_item(sc, r, nwg, xcd, xj);
         return;
       }
       if (tid == 0) {
@@ -711,7 +741,7 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
         v[1] = (__bf16)b;
         return __builtin_bit_cast(uint32_t, v);
       };
-      const WeightDesc& wd = p.wtab[cur.g];
+      const const_ptr<WeightDesc> wd = as_const(p.wtab) + cur.g;
       // four bf16 scales from column c on
       auto scales = [&](const uint16_t* s, int c) {
         uint2 v;  // the caller's scales are 2-byte aligned
@@ -725,13 +755,13 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
         if constexpr (FP8) {
           if constexpr (GATED) {
             const int c = cur.nti * (kBN / 2) + wn * 32 + b * 16 + hh * 4;
-            sg = scales(wd.s_gu, c);
+            sg = scales(wd->s_gu, c);
             // the up scales start at element n_out, a multiple of 64
-            su = scales(wd.s_gu + n_out, c);
+            su = scales(wd->s_gu + n_out, c);
           } else {
             const int c = cur.nti * kBN + b * 128 + wn * 32 + hh * 4;
-            sg = scales(wd.s_down, c);
-            su = scales(wd.s_down, c + 16);
+            sg = scales(wd->s_down, c);
+            su = scales(wd->s_down, c + 16);
           }
         }
 #pragma unroll
@@ -787,7 +817,7 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
 
     r += 1;
     if (!has_next) {
-      item = round_item(sc, r, nwg, xcd, xj);
+      item = nth_item(sc, r, nwg, xcd, xj);
       if (!split) {
         if (grp == 0) slot_barrier();  // the groups are in step again
         wait_vmcnt<0>();               // no load still targets the ring
@@ -824,9 +854,11 @@ __global__ __launch_bounds__(512, 2) void ffn_mfma_kernel(const FfnParams p) {
   const int nwg = gridDim.x;
   const int xcd = blockIdx.x & 7, xj = blockIdx.x >> 3;
   Sched sc;
-  make_sched(sc, p, p.tile_totals + (GATED ? 0 : 3), nwg, p.K / kBK, reinterpret_cast<int*>(smem));
+  make_sched(sc, p, as_const(p.tile_totals) + (GATED ? 0 : 3), nwg, p.K / kBK, reinterpret_cast<int*>(smem));
+  sc.full = uni(sc.items / nwg);
+  sc.mixed = sc.b1 > 0 && 6 * (sc.total - sc.b1) >= sc.b1;
   int r = 0;
-  int item = round_item(sc, r, nwg, xcd, xj);
+  int item = nth_item(sc, r, nwg, xcd, xj);
   while (item >= 0) {
     const int f = item_family(sc, item);
     if (f == 0)
