@@ -60,6 +60,7 @@ constexpr int kRouteLanes = 8;                              // lanes per token i
 constexpr int kRouteTokens = kRouteThreads / kRouteLanes;   // tokens per router workgroup
 constexpr int kMaxRouteExperts = 64;
 constexpr int kDirectPrefixBlocks = 64;  // router workgroups whose appends sum earlier counts directly
+constexpr int kFusedTokens = 128;  // fragments of up to this many tokens: routed and appended by one workgroup
 constexpr int kMaxTopK = 8;
 constexpr int kMaxGroups = 1024;
 
@@ -100,6 +101,13 @@ hipError_t launch_route(const float* logits, int T, int E, int k, int renorm, in
                         float* r_w, int32_t* r_rank, int32_t* blockcnt, int32_t* idx_out,
                         float* w_out, const int32_t* depth_cur, int32_t* depth_nxt, int32_t* done,
                         int32_t* err, hipStream_t s);
+// Both for a fragment of at most kFusedTokens tokens, in one launch (arguments
+// as below and above).
+hipError_t launch_route_append(const float* logits, int T, int E, int k, int renorm, int32_t* idx_out, float* w_out,
+                               const char* x, int64_t row_bytes, int32_t token_base, const int32_t* depth_cur,
+                               int32_t* depth_nxt, QEntry* q, int64_t q_stride, const void** tok_row,
+                               const int32_t* token_ids, int n_ids, int32_t* live, int32_t* pend, int32_t* err,
+                               hipStream_t s);
 // token_ids == nullptr: token t of the fragment is token_base + t.  Else its
 // id is token_ids[t] (< n_ids) and it claims pool entry live[id] / pend[id].
 hipError_t launch_append(const int32_t* r_idx, const float* r_w, const int32_t* r_rank,

@@ -392,20 +392,29 @@ static aep_status route_common(Ctx* c, int32_t layer, const void* x, const float
   if (ub + T > c->tmax() || L.rows + (int64_t)T * k > c->row_cap()) return AEP_ERR_CAPACITY;
   if (!want_pool && (int64_t)L.tokens + T > c->tmax()) return AEP_ERR_CAPACITY;
   hipStream_t s = as_stream(stream);
-  int32_t* ridx = c->at<int32_t>(c->off_ridx);
-  float* rw = c->at<float>(c->off_rw);
-  int32_t* rrank = c->at<int32_t>(c->off_rrank);
-  int32_t* bcnt = c->at<int32_t>(c->off_blockcnt);
-  hipError_t e1 = launch_route(logits, T, E, k, c->cfg.renorm, ridx, rw, rrank, bcnt, idx_out, w_out,
-                               c->depth(layer, L.cur), c->depth(layer, L.cur ^ 1), c->route_done(), c->err(), s);
-  if (e1 != hipSuccess) return AEP_ERR_DEVICE;
   const int64_t row_bytes = (int64_t)c->cfg.d_model * c->esz;
-  hipError_t e2 = launch_append(ridx, rw, rrank, bcnt, T, E, k, reinterpret_cast<const char*>(x), row_bytes,
-                                want_pool ? 0 : L.tokens, c->depth(layer, L.cur), c->depth(layer, L.cur ^ 1),
-                                c->q(layer), c->tmax(), c->tokrow(layer), token_ids,
-                                (int)c->tmax(), want_pool ? c->live(layer) : nullptr,
-                                want_pool ? c->pend(layer) : nullptr, c->err(), s);
-  if (e2 != hipSuccess) return AEP_ERR_DEVICE;
+  const char* rows = reinterpret_cast<const char*>(x);
+  const int32_t base = want_pool ? 0 : L.tokens;
+  int32_t* live = want_pool ? c->live(layer) : nullptr;
+  int32_t* pend = want_pool ? c->pend(layer) : nullptr;
+  int32_t *cur = c->depth(layer, L.cur), *nxt = c->depth(layer, L.cur ^ 1);
+  if (T <= kFusedTokens) {
+    if (launch_route_append(logits, T, E, k, c->cfg.renorm, idx_out, w_out, rows, row_bytes, base, cur, nxt,
+                            c->q(layer), c->tmax(), c->tokrow(layer), token_ids, (int)c->tmax(), live, pend, c->err(),
+                            s) != hipSuccess)
+      return AEP_ERR_DEVICE;
+  } else {
+    int32_t* ridx = c->at<int32_t>(c->off_ridx);
+    float* rw = c->at<float>(c->off_rw);
+    int32_t* rrank = c->at<int32_t>(c->off_rrank);
+    int32_t* bcnt = c->at<int32_t>(c->off_blockcnt);
+    if (launch_route(logits, T, E, k, c->cfg.renorm, ridx, rw, rrank, bcnt, idx_out, w_out, cur, nxt, c->route_done(),
+                     c->err(), s) != hipSuccess)
+      return AEP_ERR_DEVICE;
+    if (launch_append(ridx, rw, rrank, bcnt, T, E, k, rows, row_bytes, base, cur, nxt, c->q(layer), c->tmax(),
+                      c->tokrow(layer), token_ids, (int)c->tmax(), live, pend, c->err(), s) != hipSuccess)
+      return AEP_ERR_DEVICE;
+  }
   L.cur ^= 1;
   if (!want_pool) L.tokens += T;
   L.pool = want_pool;
