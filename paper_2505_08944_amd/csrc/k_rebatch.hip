@@ -3,18 +3,21 @@
 // plan: workgroup 0 reads the drained layer's per-expert queue depths (or one
 // expert's, for a single-expert drain) with one thread per group, and writes
 // counts / exclusive-scan offsets / the FFN group table (row-tile families
-// and tile ranges) from workgroup-wide scans, then the group of every tile of
-// both FFN launches (a binary search of the family's tile starts in LDS per
-// tile, all threads); it resets the drained queue depths to zero.  All
-// workgroups clear the (token, slot) -> row map.
+// and tile ranges), then the group of every tile of both FFN launches (a run
+// of tiles per group, family and launch); it resets the drained queue depths
+// to zero.  All workgroups clear the (token, slot) -> row map.  The launch is
+// one chain of latencies (depths, scan, table), so the chain is kept short:
+// scans by DPP, one barrier for up to 64 groups and no search per tile (66
+// groups, 8192 tokens 11.9 -> 7.5 us; 8 groups, 4.6 us).
 //
-// gather: one wave per batch row.  A routed row finds its expert by binary
-// search over the offsets, reads its queue entry and copies the referenced
-// row (16-byte vector loads/stores, the whole wave on one row, so each row is
-// one contiguous coalesced stream; up to 4 loads per lane in flight before
-// the stores); lane 0 records the row's token and gate weight and the
-// (token, slot) -> row map.  Shared-expert rows copy every token's row in id
-// order.
+// gather: one wave per batch row.  A routed row finds its expert from the
+// offsets (up to 64 experts: one lane per offset and a ballot, no LDS and no
+// barrier before the row's own loads; more: binary search in LDS), reads its
+// queue entry and copies the referenced row (16-byte vector loads/stores, the
+// whole wave on one row, so each row is one contiguous coalesced stream; up
+// to 8 loads per lane in flight before the stores); lane 0 records the row's
+// token and gate weight and the (token, slot) -> row map.  Shared-expert rows
+// copy every token's row in id order.
 #include <algorithm>
 
 #include "aep_internal.h"
@@ -23,47 +26,16 @@ namespace aep {
 
 constexpr int kPlanThreads = 1024;
 
-// Exclusive scan of NV ints per thread over a workgroup of kPlanThreads
-// threads (inclusive wave scans with shuffles, then a scan of the wave
-// totals by NV threads); `total` receives the workgroup sums.  wsum holds
-// kPlanThreads / 64 + 1 rows.
-template <int NV>
-__device__ __forceinline__ void plan_block_scan(int (&v)[NV], int (&total)[NV],
-                                                int32_t (*wsum)[NV]) {
-  constexpr int kWaves = kPlanThreads / 64;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int inc[NV];
-#pragma unroll
-  for (int i = 0; i < NV; ++i) inc[i] = v[i];
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int y = __shfl_up(inc[i], off);
-      if (lane >= off) inc[i] += y;
-    }
-  }
-  if (lane == 63)
-#pragma unroll
-    for (int i = 0; i < NV; ++i) wsum[wave][i] = inc[i];
-  __syncthreads();
-  if (threadIdx.x < NV) {
-    const int i = threadIdx.x;
-    int acc = 0;
-    for (int w = 0; w < kWaves; ++w) {
-      const int x = wsum[w][i];
-      wsum[w][i] = acc;
-      acc += x;
-    }
-    wsum[kWaves][i] = acc;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    v[i] = wsum[wave][i] + inc[i] - v[i];
-    total[i] = wsum[kWaves][i];
-  }
-  __syncthreads();
+// Inclusive sum over the lanes of a wave: rows of 16 by shifts, then the last
+// lane of the row and of the half before.
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111 /* row_shr 1 */, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112 /* row_shr 2 */, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114 /* row_shr 4 */, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118 /* row_shr 8 */, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142 /* row_bcast 15 */, 0xA, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143 /* row_bcast 31 */, 0xC, 0xF, false);
+  return v;
 }
 
 // Workgroup 0 plans the drain, one thread per group; every workgroup clears
@@ -80,118 +52,165 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(int E, int S, int n_
                                                             int64_t tile_cap,
                                                             int32_t* __restrict__ pos,
                                                             float* __restrict__ posw) {
-  const int tid = threadIdx.x;
-  if (blockIdx.x == 0) {
-    __shared__ int32_t wsum7[kPlanThreads / 64 + 1][7];
-    const int G = E + S;
-    const int g = tid;
-    const bool real = g < G;
-    const int n = !real ? 0 : g < E ? (only_expert < 0 || g == only_expert ? depth[g] : 0) : n_tokens;
-    // full blocks, and the remainder in one tile of the smallest family that
-    // holds it
-    const int full = n / bm, rem = n - full * bm;
-    int nrt[3] = {full, 0, 0};
-    if (families == 1 || rem > bm / 2)
-      nrt[0] += rem > 0 ? 1 : 0;
-    else if (rem > bm / 4)
-      nrt[1] = 1;
-    else if (rem > 0)
-      nrt[2] = 1;
-    int b[7];
-    b[0] = n;
-#pragma unroll
-    for (int i = 0; i < 6; ++i) b[1 + i] = nrt[i % 3] * (i < 3 ? nt0 : nt1);
-    int sum7[7];
-    plan_block_scan<7>(b, sum7, wsum7);
-    if (real) {
-      GroupDesc gd;
-      gd.n = n;
-      // shared groups all read the token rows that follow the routed ones
-      gd.x_row0 = b[0];
-      gd.y_row0 = b[0];
-#pragma unroll
-      for (int i = 0; i < 6; ++i) gd.t0[i] = b[1 + i];
-#pragma unroll
-      for (int f = 0; f < 3; ++f) gd.nrt[f] = nrt[f];
-      gd.row1 = full * bm;
-      gd.pad[0] = gd.pad[1] = gd.pad[2] = 0;
-      if (g >= E) gd.x_row0 = b[0] - (g - E) * n_tokens;
-      groups[g] = gd;
-      counts[g] = n;
-      offsets[g] = b[0];
-    }
-    if (g == 0) {
-      offsets[G] = sum7[0];
-#pragma unroll
-      for (int i = 0; i < 6; ++i) tile_totals[i] = sum7[1 + i];
-    }
-    // The group of every tile of both launches (tiles are numbered per
-    // launch, family by family): the last
-    // group whose first tile in that family is not above the tile.
-    __shared__ int32_t t0s[6][kMaxGroups + 1];
-    if (real)
-#pragma unroll
-      for (int i = 0; i < 6; ++i) t0s[i][g] = b[1 + i];
-    if (g == 0)
-#pragma unroll
-      for (int i = 0; i < 6; ++i) t0s[i][G] = sum7[1 + i];
-    __syncthreads();
-#pragma unroll
-    for (int st = 0; st < 2; ++st) {
-      const int tot0 = sum7[1 + 3 * st], tot1 = sum7[2 + 3 * st], tot2 = sum7[3 + 3 * st];
-      for (int t = tid; t < tot0 + tot1 + tot2; t += kPlanThreads) {
-        const int f = t < tot0 ? 0 : (t < tot0 + tot1 ? 1 : 2);
-        const int local = t - (f == 0 ? 0 : (f == 1 ? tot0 : tot0 + tot1));
-        const int32_t* t0 = t0s[3 * st + f];
-        int lo = 0, hi = G;  // t0[lo] <= local < t0[hi]
-        while (hi - lo > 1) {
-          const int mid = (lo + hi) >> 1;
-          if (t0[mid] <= local)
-            lo = mid;
-          else
-            hi = mid;
-        }
-        tile_group[st * tile_cap + t] = lo;
-      }
-    }
-    // The drained queues are empty again, in both halves of the depth
-    // ping-pong: whichever half the next append reads starts from zero (so a
-    // captured drain step replays correctly whatever the parity of its
-    // appends).  Every read of depth above precedes the scans' barriers.
-    if (g < E && (only_expert < 0 || g == only_expert)) depth[g] = depth_other[g] = 0;
-  }
+  constexpr int kWaves = kPlanThreads / 64;
+  const int tid = threadIdx.x, wave = tid >> 6;
+  const int G = E + S;
+  const int g = tid;
+  const bool real = blockIdx.x == 0 && g < G;
+  const int n = !real ? 0 : g < E ? (only_expert < 0 || g == only_expert ? depth[g] : 0) : n_tokens;
+
   const int64_t nk = (int64_t)n_tokens * k;
   for (int64_t i = (int64_t)blockIdx.x * kPlanThreads + tid; i < nk; i += (int64_t)gridDim.x * kPlanThreads) {
     pos[i] = -1;
     posw[i] = 0.f;
   }
+  if (blockIdx.x != 0) return;
+
+  // full blocks, and the remainder in one tile of the smallest family that
+  // holds it
+  const int full = n / bm, rem = n - full * bm;
+  int nrt[3] = {full, 0, 0};
+  if (families == 1 || rem > bm / 2)
+    nrt[0] += rem > 0 ? 1 : 0;
+  else if (rem > bm / 4)
+    nrt[1] = 1;
+  else if (rem > 0)
+    nrt[2] = 1;
+  // rows and row tiles per family of the groups before this one, and of all
+  __shared__ int32_t wsum[kWaves][4];
+  __shared__ int32_t first[3][kMaxGroups + 1];  // a group's first row tile per family
+  int inc[4] = {n, nrt[0], nrt[1], nrt[2]};
+  if (G > 64 || wave == 0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) inc[i] = wave_scan(inc[i]);
+  }
+  if (G > 64) {
+    if ((tid & 63) == 63)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) wsum[wave][i] = inc[i];
+    __syncthreads();
+    int before[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int w = 0; w < kWaves - 1; ++w)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) before[i] += w < wave ? wsum[w][i] : 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) inc[i] += before[i];
+  }
+  if (real) {
+    GroupDesc gd;
+    gd.n = n;
+    // shared groups all read the token rows that follow the routed ones
+    const int row0 = inc[0] - n;
+    gd.x_row0 = g >= E ? row0 - (g - E) * n_tokens : row0;
+    gd.y_row0 = row0;
+#pragma unroll
+    for (int f = 0; f < 3; ++f) {
+      const int t0 = inc[1 + f] - nrt[f];
+      first[f][g] = t0;
+      gd.t0[f] = t0 * nt0;
+      gd.t0[3 + f] = t0 * nt1;
+      gd.nrt[f] = nrt[f];
+    }
+    gd.row1 = full * bm;
+    gd.pad[0] = gd.pad[1] = gd.pad[2] = 0;
+    groups[g] = gd;
+    counts[g] = n;
+    offsets[g] = row0;
+    if (g == G - 1) {
+      offsets[G] = inc[0];
+#pragma unroll
+      for (int f = 0; f < 3; ++f) {
+        first[f][G] = inc[1 + f];
+        tile_totals[f] = inc[1 + f] * nt0;
+        tile_totals[3 + f] = inc[1 + f] * nt1;
+      }
+    }
+    // The drained queues are empty again, in both halves of the depth
+    // ping-pong: whichever half the next append reads starts from zero (so a
+    // captured drain step replays correctly whatever the parity of its
+    // appends).
+    if (g < E && (only_expert < 0 || g == only_expert)) depth[g] = depth_other[g] = 0;
+  }
+  __syncthreads();
+  // The group of every tile of both launches (tiles are numbered per launch,
+  // family by family): a group's tiles of a family follow one another, written
+  // by one wave, or by several where there are fewer groups than waves.
+  const int per = G < kWaves ? kWaves / G : 1;
+  for (int h = wave / per; h < G; h += kWaves / per) {
+    int base = 0;
+#pragma unroll
+    for (int f = 0; f < 3; ++f) {
+      const int lo = first[f][h], hi = first[f][h + 1], all = first[f][G];
+      const int lane = (wave % per) * 64 + (tid & 63);
+      for (int t = lo * nt0 + lane; t < hi * nt0; t += per * 64) tile_group[(int64_t)base * nt0 + t] = h;
+      for (int t = lo * nt1 + lane; t < hi * nt1; t += per * 64) tile_group[tile_cap + (int64_t)base * nt1 + t] = h;
+      base += all;
+    }
+  }
 }
 
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(1))) v4u* gsrc_t;
+
+// N 16-byte chunks per lane of a row from chunk c0 on, every load issued
+// before the first store (the source rows are global memory; the stores cannot
+// alias them).  FULL: all of them exist.
+template <int N, bool FULL>
+__device__ __forceinline__ void copy_pass(gsrc_t src, v4u* dst, int c0, int nchunk) {
+  const int c = c0 + (threadIdx.x & 63);
+  v4u v[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (FULL || c + 64 * i < nchunk) v[i] = src[c + 64 * i];
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (FULL || c + 64 * i < nchunk) dst[c + 64 * i] = v[i];
+}
+
+// LANES: E <= 64, an offset per lane.  57344 rows of 4 KB take 71 us, 3.3 TB/s
+// of stores beside as much read from the Infinity Cache (a row is read once
+// per selected expert); two or four rows per wave in flight took 72.
+template <bool LANES>
 __global__ __launch_bounds__(256) void gather_kernel(
     const QEntry* __restrict__ q, int64_t q_stride, const int32_t* __restrict__ offsets, int E,
     int64_t N, int n_tokens, int shared, const void* const* __restrict__ tok_row, char* xp,
     int64_t row_bytes, int32_t* __restrict__ row_token, float* __restrict__ row_w,
     int32_t* __restrict__ pos, float* __restrict__ posw, int k, int32_t* __restrict__ err) {
-  __shared__ int32_t off_s[kMaxGroups + 1];
-  for (int i = threadIdx.x; i <= E; i += blockDim.x) off_s[i] = offsets[i];
-  __syncthreads();
+  __shared__ int32_t off_s[LANES ? 1 : kMaxGroups + 1];
   const int lane = threadIdx.x & 63;
-  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  int my_off = 0;  // LANES: offsets[lane + 1], those past E equal to the last
+  if constexpr (LANES) {
+    my_off = offsets[min(lane + 1, E)];
+  } else {
+    for (int i = threadIdx.x; i <= E; i += blockDim.x) off_s[i] = offsets[i];
+    __syncthreads();
+  }
+  const int64_t r = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t R = N + (shared ? n_tokens : 0);
   if (r >= R) return;
-  if (r < N && r >= off_s[E]) return;  // N only bounds the routed rows
-  const uint4* src;
+  const int routed = LANES ? __builtin_amdgcn_readlane(my_off, 63) : off_s[E];
+  if (r < N && r >= routed) return;  // N only bounds the routed rows
+  const void* row;
   if (r < N) {
-    int lo = 0, hi = E;  // off_s[lo] <= r < off_s[hi]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (off_s[mid] <= r)
-        lo = mid;
-      else
-        hi = mid;
+    int lo = 0, at;  // the row's expert, and its place in the expert's queue
+    if constexpr (LANES) {
+      // r < routed, so the offsets not above it are those of lo experts
+      lo = __popcll(__ballot(my_off <= r));
+      at = (int)r - (lo > 0 ? __builtin_amdgcn_readlane(my_off, lo - 1) : 0);
+    } else {
+      int hi = E;  // off_s[lo] <= r < off_s[hi]
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (off_s[mid] <= r)
+          lo = mid;
+        else
+          hi = mid;
+      }
+      at = (int)r - off_s[lo];
     }
-    const QEntry en = q[(int64_t)lo * q_stride + (r - off_s[lo])];
-    src = reinterpret_cast<const uint4*>(en.row);
+    const QEntry en = q[(int64_t)lo * q_stride + at];
+    row = en.row;
     if (lane == 0) {
       const int tok = en.token_slot & kTokenMask;
       const int slot = (int)((uint32_t)en.token_slot >> kTokenBits);
@@ -205,26 +224,18 @@ __global__ __launch_bounds__(256) void gather_kernel(
       }
     }
   } else {
-    src = reinterpret_cast<const uint4*>(tok_row[r - N]);
+    row = tok_row[r - N];
   }
-  // all of a pass's loads are issued before its stores (the source rows are
-  // global memory; the stores cannot alias them)
-  typedef unsigned v4u __attribute__((ext_vector_type(4)));
-  typedef const __attribute__((address_space(1))) v4u* gsrc_t;
-  const gsrc_t gsrc = (gsrc_t)src;
+  const gsrc_t src = (gsrc_t)row;
   v4u* dst = reinterpret_cast<v4u*>(xp + r * row_bytes);
   const int nchunk = (int)(row_bytes >> 4);
-  constexpr int kB = 4;  // 16-byte chunks per lane per pass
   int c0 = 0;
-  for (; c0 + 64 * kB <= nchunk; c0 += 64 * kB) {
-    // a full pass: every load is issued before the first store
-    v4u v[kB];
-#pragma unroll
-    for (int i = 0; i < kB; ++i) v[i] = gsrc[c0 + lane + 64 * i];
-#pragma unroll
-    for (int i = 0; i < kB; ++i) dst[c0 + lane + 64 * i] = v[i];
+  for (; c0 + 512 <= nchunk; c0 += 512) copy_pass<8, true>(src, dst, c0, nchunk);
+  if (c0 + 256 <= nchunk) {
+    copy_pass<4, true>(src, dst, c0, nchunk);
+    c0 += 256;
   }
-  for (int c = c0 + lane; c < nchunk; c += 64) dst[c] = gsrc[c];  // the row's tail
+  if (c0 < nchunk) copy_pass<4, false>(src, dst, c0, nchunk);
 }
 
 hipError_t launch_plan(int E, int S, int n_tokens, int k, int only_expert, int32_t* depth,
@@ -247,8 +258,12 @@ hipError_t launch_gather(const QEntry* q, int64_t q_stride, const int32_t* offse
   const int64_t R = N + (shared ? n_tokens : 0);
   if (R == 0) return hipSuccess;
   const int64_t nb = (R + 3) / 4;
-  gather_kernel<<<(unsigned)nb, 256, 0, s>>>(q, q_stride, offsets, E, N, n_tokens, shared, tok_row,
-                                             xp, row_bytes, row_token, row_w, pos, posw, k, err);
+  if (E <= 64)
+    gather_kernel<true><<<(unsigned)nb, 256, 0, s>>>(q, q_stride, offsets, E, N, n_tokens, shared, tok_row, xp,
+                                                     row_bytes, row_token, row_w, pos, posw, k, err);
+  else
+    gather_kernel<false><<<(unsigned)nb, 256, 0, s>>>(q, q_stride, offsets, E, N, n_tokens, shared, tok_row, xp,
+                                                      row_bytes, row_token, row_w, pos, posw, k, err);
   return hipGetLastError();
 }
 
