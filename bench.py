@@ -377,7 +377,7 @@ def main():
     achieved = gu_flops / gu_s / 1e12
     ffn_s = (stage_ms["gate_up"] + stage_ms["down"]) / 1e3
     tr = traffic_record(args.workload)
-    kname = {"bf16": "aep::ffn_dlds_kernel<true, false>", "fp8": "aep::ffn_dlds_kernel<true, true>"}.get(
+    kname = {"bf16": "aep::ffn_mfma_kernel<true, false>", "fp8": "aep::ffn_mfma_kernel<true, true>"}.get(
         w.wdt, "aep::ffn_f32_kernel<true>")
     roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved / PEAK_BF16_TFLOPS, 4),

@@ -127,8 +127,8 @@ aep_status aep_workspace_size(const aep_ctx* ctx, size_t* bytes);
  * bytes, 256-byte aligned, on the current HIP device.  Initialises it on
  * `stream` and waits for that.  Resets every queue.  The workspace holds the
  * mu-queues, weight tables, the batch buffers, the FFN intermediate and (bf16
- * activations) 32 MiB for the split-K partial sums of FFN launches with few
- * tiles. */
+ * activations) 32 MiB for the split-K partial sums of the FFN launches' last
+ * rounds. */
 aep_status aep_bind_workspace(aep_ctx* ctx, void* d_ws, size_t bytes, void* stream);
 
 /* For callers that cannot allocate device memory (code under HIP graph
@@ -315,9 +315,9 @@ aep_status aep_rebatch(aep_ctx* ctx, int32_t layer, aep_batch* out, void* stream
 /* Expert FFN of a batch: every group g computes, on its rows,
  * y = W_down (silu(W_gate x) * (W_up x)), silu(v) = v / (1 + e^-v), with
  * f32 accumulation; the intermediate h is rounded to the act dtype.
- * y: device [n_rows][d] act dtype, caller-owned.  A launch with few tiles
- * (bf16 and fp8 weights) splits its reduction into pieces whose f32 partial
- * sums are added in a fixed order, so results are reproducible run to run;
+ * y: device [n_rows][d] act dtype, caller-owned.  A launch's last, partial
+ * round of tiles (bf16 and fp8 weights) splits its reduction into pieces whose
+ * f32 partial sums are added in a fixed order, so results are reproducible;
  * its per-tile counters live in the workspace, so FFN launches of one
  * context must not overlap on the GPU (issue them in stream order). */
 aep_status aep_expert_ffn(aep_ctx* ctx, const aep_batch* batch, void* y, void* stream);
