@@ -541,12 +541,12 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
     if constexpr (NU == 2) load_a(1, s);
     st.next();
   }
+  wait_vmcnt<kFlight>();
+  slot_barrier();
   if constexpr (FAM == 0) {
-    wait_vmcnt<kFlight>();
-    slot_barrier();
     read_b(2, 0);
-  } else {
-    wait_vmcnt<kFlight>();
+    // the first phase refills this unit, each wave for another one's reads too
+    wait_lgkm0();
     slot_barrier();
   }
   if (grp == 1) slot_barrier();
