@@ -76,6 +76,13 @@ constexpr int kFfnLds = 160 * 1024;  // LDS of one FFN workgroup (the CU's)
 constexpr int kMaxSplit = 8;
 constexpr int kMinSplitSteps = 8;
 constexpr int kSplitCounters = 1024;
+// Words of the tile totals' array: 6 totals, then the cut of each stage's last
+// round (see ffn_sched.h).
+constexpr int kCutWord = 6;
+constexpr int kTileWords = 8;
+// Workgroups of a bf16 / fp8 FFN launch: one per CU, a multiple of 8 (the map
+// from XCDs to items needs that).
+inline int ffn_grid(int num_cu) { return num_cu < 8 ? 8 : (num_cu + 7) & ~7; }
 // The partial sums' area of a context: 128 parts of a 256-row tile (a tile of
 // n pieces needs n - 1 parts; the kernel picks a split that fits).
 constexpr int64_t kSplitBytes = 128 * (int64_t)kBM * kBN * 4;
@@ -127,8 +134,9 @@ hipError_t launch_enqueue_rows(const char* rows, int64_t row_bytes, const int32_
                                int k, int expert, int E, const int32_t* depth_cur,
                                int32_t* depth_nxt, QEntry* q, int64_t q_stride, int32_t* err,
                                hipStream_t s);
-// tile_totals[6]: tiles per (stage, family), index stage * 3 + family (stage
-// 0 gate/up, 1 down).  nt[2]: column tiles per row tile of each stage.
+// tile_totals[kTileWords]: tiles per (stage, family), index stage * 3 + family
+// (stage 0 gate/up, 1 down), then the cuts, not chosen yet.  nt[2]: column
+// tiles per row tile of each stage.
 // bm: rows of a family 0 tile; families: 3, or 1 (f32: every row in family 0).
 // only_expert >= 0: drain that expert's queue alone (every other group gets
 // 0 rows and keeps its queue).  depth is the current half of the layer's
@@ -142,11 +150,18 @@ hipError_t launch_plan(int E, int S, int n_tokens, int k, int only_expert, int32
                        int32_t* tile_totals, const int* nt, int bm, int families, int32_t* tile_group, int64_t tile_cap, int32_t* pos, float* posw,
                        hipStream_t s);
 // N bounds the routed rows (the exact count is offsets[E] on the device);
-// pos == nullptr skips the (token, slot) -> row map.
+// pos == nullptr skips the (token, slot) -> row map.  A few extra workgroups
+// choose how each FFN launch's last round is cut (cut.nwg == 0: none do).
+struct CutArgs {
+  int32_t* tile_totals;
+  int nwg;              // workgroups of the FFN launches
+  int kt[2];            // K steps per stage
+  int64_t split_bytes;  // room for partial sums
+};
 hipError_t launch_gather(const QEntry* q, int64_t q_stride, const int32_t* offsets, int E,
                          int64_t N, int n_tokens, int shared, const void* const* tok_row,
                          char* xp, int64_t row_bytes, int32_t* row_token, float* row_w,
-                         int32_t* pos, float* posw, int k, int32_t* err, hipStream_t s);
+                         int32_t* pos, float* posw, int k, int32_t* err, const CutArgs& cut, hipStream_t s);
 // token pool: rows [0, offsets[E]) of a batch (N bounds them) are merged into
 // pool[row_token[r]]; release writes out / ready for completed ids.
 hipError_t launch_pool_accumulate(int act_dtype, const void* y, int64_t N, const int32_t* offsets,
@@ -156,16 +171,14 @@ hipError_t launch_pool_release(int act_dtype, float* pool, int32_t* live, int32_
                                void* out, int32_t* ready, int d, hipStream_t s);
 // stage 0: gate/up (xp -> h), stage 1: down (h -> y); max_tiles bounds the
 // stage's tile count (the exact count is on the device); tile_group is that
-// stage's row of the plan's tile -> group map.  split_slots (split_bytes
-// bytes) holds the split-K partial sums and split_cnt [kSplitCounters] the
-// arrivals per split tile, zero before the launch and left zero (bf16 / fp8
-// weights; split_slots == nullptr: no split).
+// stage's row of the plan's tile -> group map.  split_slots holds the split-K
+// partial sums and split_cnt [kSplitCounters] the arrivals per split tile,
+// zero before the launch and left zero (bf16 / fp8 weights).
 // clk != nullptr: workgroup w < clk_n writes its elapsed (s_memtime,
 // s_memrealtime) ticks to clk[2w], clk[2w + 1] (bf16 / fp8 weights only).
 hipError_t launch_ffn(int stage, int act_dtype, int w_dtype, const GroupDesc* groups,
-                      const WeightDesc* wtab, int G, const int32_t* tile_totals,
-                      const int32_t* tile_group, float* split_slots, int32_t* split_cnt,
-                      int64_t split_bytes, int max_tiles,
+                      const WeightDesc* wtab, const int32_t* tile_totals, const int32_t* tile_group,
+                      float* split_slots, int32_t* split_cnt, int max_tiles,
                       const void* xp, void* h, void* y, int d, int f, int num_cu,
                       unsigned long long* clk, int clk_n, hipStream_t s);
 hipError_t launch_combine(int act_dtype, const void* y, int64_t N, int n_tokens, int S, int k,

@@ -124,6 +124,15 @@ int64_t tile_bound(const Ctx& c, int stage, int64_t N, int64_t T) {
   return (N / bm + std::min<int64_t>(E, N) + S * ((T + bm - 1) / bm)) * nt[stage];
 }
 
+// What the re-batch needs to choose how the FFN launches cut their last rounds
+// (f32 launches do not).
+CutArgs cut_args(Ctx& c) {
+  return CutArgs{c.at<int32_t>(c.off_tiles),
+                 c.cfg.act_dtype == AEP_F32 ? 0 : ffn_grid(c.num_cu),
+                 {c.cfg.d_model / kBK, c.cfg.d_ffn / kBK},
+                 (int64_t)c.split_bytes};
+}
+
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 bool layout(Ctx& c) {
@@ -153,7 +162,7 @@ bool layout(Ctx& c) {
   c.off_counts = take(sizeof(int32_t) * c.G);
   c.off_offsets = take(sizeof(int32_t) * (c.G + 1));
   c.off_groups = take(sizeof(GroupDesc) * c.G);
-  c.off_tiles = take(sizeof(int32_t) * 6);
+  c.off_tiles = take(sizeof(int32_t) * kTileWords);
   c.tile_cap = std::max(tile_bound(c, 0, N, T), tile_bound(c, 1, N, T));
   c.off_tilegrp = take(sizeof(int32_t) * 2 * c.tile_cap);
   c.off_xp = take((size_t)xrows * d * c.esz);
@@ -566,7 +575,7 @@ aep_status aep_rebatch(aep_ctx* ctx, int32_t layer, aep_batch* out, void* stream
   const int64_t row_bytes = (int64_t)c->cfg.d_model * c->esz;
   if (launch_gather(c->q(layer), c->tmax(), offsets, E, L.rows, L.tokens, S > 0, c->tokrow(layer),
                     c->at<char>(c->off_xp), row_bytes, c->at<int32_t>(c->off_rowtok), c->at<float>(c->off_roww),
-                    pos, posw, k, c->err(), s) != hipSuccess)
+                    pos, posw, k, c->err(), cut_args(*c), s) != hipSuccess)
     return AEP_ERR_DEVICE;
   c->epoch += 1;
   c->batch_out = true;
@@ -613,7 +622,7 @@ aep_status aep_rebatch_expert(aep_ctx* ctx, int32_t layer, int32_t expert, aep_b
   const int64_t row_bytes = (int64_t)c->cfg.d_model * c->esz;
   if (launch_gather(c->q(layer), c->tmax(), offsets, E, nb, 0, 0, c->tokrow(layer), c->at<char>(c->off_xp),
                     row_bytes, c->at<int32_t>(c->off_rowtok), c->at<float>(c->off_roww), nullptr, nullptr, k,
-                    c->err(), s) != hipSuccess)
+                    c->err(), cut_args(*c), s) != hipSuccess)
     return AEP_ERR_DEVICE;
   c->epoch += 1;
   c->batch_out = true;
@@ -653,10 +662,10 @@ static aep_status ffn_stage(Ctx* c, const aep_batch* batch, int stage, void* y, 
   const int64_t mt = tile_bound(*c, stage, batch->n_routed, batch->n_tokens);
   if (mt > INT32_MAX || mt > c->tile_cap) return AEP_ERR_UNSUPPORTED;
   return dev(launch_ffn(stage, c->cfg.act_dtype, c->cfg.w_dtype, c->at<GroupDesc>(c->off_groups),
-                        c->wtab(batch->layer), c->G, c->at<int32_t>(c->off_tiles),
+                        c->wtab(batch->layer), c->at<int32_t>(c->off_tiles),
                         c->at<int32_t>(c->off_tilegrp) + stage * c->tile_cap,
                         c->split_bytes ? c->at<float>(c->off_split) : nullptr,
-                        c->split_bytes ? c->at<int32_t>(c->off_splitcnt) : nullptr, (int64_t)c->split_bytes, (int)mt,
+                        c->split_bytes ? c->at<int32_t>(c->off_splitcnt) : nullptr, (int)mt,
                         c->ws + c->off_xp, c->ws + c->off_h, y, c->cfg.d_model, c->cfg.d_ffn, c->num_cu,
                         c->clk, c->clk_n, as_stream(stream)));
 }

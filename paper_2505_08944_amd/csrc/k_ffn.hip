@@ -33,7 +33,7 @@
 #include <algorithm>
 
 #include "aep_device.h"
-#include "aep_internal.h"
+#include "ffn_sched.h"
 
 namespace aep {
 
@@ -46,13 +46,12 @@ struct FfnParams {
   const GroupDesc* groups;
   const WeightDesc* wtab;
   const int32_t* tile_totals;
+  const uint32_t* cut;        // how the last round is cut (written with the re-batch)
   const int32_t* tile_group;  // group of each tile of this launch (written by the plan)
-  float* split_slots;         // split-K partial sums (nullptr: no split)
+  float* split_slots;         // split-K partial sums
   int32_t* split_cnt;         // pieces finished per tile (zero between launches)
-  int64_t split_bytes;        // size of split_slots
   const void* a;  // x_perm (gate/up) or h (down)
   void* out;      // h (gate/up) or y (down)
-  int G;
   int K;      // reduction length: d (gate/up) or f (down)
   int n_out;  // output columns: f (gate/up) or d (down)
   unsigned long long* clk;  // clock probe (nullptr: off)
@@ -103,9 +102,6 @@ __device__ __forceinline__ void dload16(i32x4_t rsrc, uint32_t voff, uint32_t so
                : "memory", "m0");
 }
 
-// A wave-uniform value, in a scalar register whatever unit computed it.
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
 // s_waitcnt with only vmcnt (or only lgkmcnt) constrained (gfx9 encoding).
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
@@ -139,136 +135,6 @@ __device__ __forceinline__ void panel_decode(int local, int nrow, int ncol, int&
   const int w = min(PANEL, ncol - pi * PANEL);  // the last panel may be narrower
   rt = within / w;
   ct = pi * PANEL + (within - rt * w);
-}
-
-// ------------------------------------------------------------ work division
-// Tiles are numbered family by family (256, 128, 64 rows).  The first
-// `whole` of them -- full rounds of the grid -- are one work item each.  The
-// others, a partial round, would leave CUs idle: they are cut along K into
-// nsp[family] pieces (at least kMinSplitSteps steps each), whose f32 partial
-// sums meet in the workspace.  Items are dealt round by round; odd rounds in
-// reverse, so that a workgroup that got one of a round's larger items gets
-// one of the next round's smaller ones.
-struct Sched {
-  int b1, b2, total;  // first tile of families 1 and 2, and the number of tiles
-  int whole, items;
-  int full;           // full rounds of items
-  bool mixed;         // 256-row tiles beside a sixth as many smaller ones or more
-  int nsp;            // pieces per tail tile: family f in bits 4f .. 4f + 3
-  __device__ __forceinline__ int first(int f) const { return f == 0 ? 0 : f == 1 ? b1 : f == 2 ? b2 : total; }
-  // first tail tile of family f and how many there are
-  __device__ __forceinline__ int tail0(int f) const { return max(first(f), whole); }
-  __device__ __forceinline__ int tail(int f) const { return max(0, first(f + 1) - tail0(f)); }
-  __device__ __forceinline__ int pieces(int f) const { return (nsp >> (4 * f)) & 15; }
-};
-
-// Relative cost of one K step of a tile per family: a 256-row step is bound
-// by its MFMAs, the smaller ones by the CU's load path (64, 48 and 40 KB per
-// step), and the cost of a split tile's partial sums in the same unit.
-__device__ __forceinline__ int step_cost(int f) { return f == 0 ? 8 : f == 1 ? 6 : 5; }
-
-__device__ __forceinline__ int fam_floats(int f) { return (kBM * kBN) >> f; }
-__device__ __forceinline__ int piece_cost(int f, int KT, int n) {
-  return (int)((float)(step_cost(f) * KT) * __builtin_amdgcn_rcpf((float)n)) + (n > 1 ? (40 + 20 * n) >> f : 0);
-}
-
-__device__ __forceinline__ int item_family(const Sched& s, int item) {
-  if (item < s.whole) return item < s.b1 ? 0 : (item < s.b2 ? 1 : 2);
-  const int j = item - s.whole;
-  const int m0 = s.tail(0) * s.pieces(0), m1 = s.tail(1) * s.pieces(1);
-  return j < m0 ? 0 : (j < m0 + m1 ? 1 : 2);
-}
-
-// Work item of workgroup slot lin (XCD-blocked: lin / (nwg / 8) is its XCD)
-// in round r, -1 for none.
-__device__ __forceinline__ int round_item(const Sched& s, int r, int nwg, int xcd, int xj) {
-  const int base = r * nwg;
-  const int cnt = s.items - base;
-  if (cnt <= 0) return -1;
-  const int lin = xcd * (nwg >> 3) + xj;
-  const int rl = (r & 1) ? nwg - 1 - lin : lin;
-  if (cnt >= nwg) return base + rl;
-  // a partial round: over all XCDs, unless the round before it was a mix of
-  // families; then the workgroups that had its smaller items come first
-  if (r > 0 && item_family(s, base - nwg) != item_family(s, base - 1)) return rl < cnt ? base + rl : -1;
-  const int q = (cnt + 7) >> 3;
-  const int idx = xcd * q + xj;
-  return xj < q && idx < cnt ? base + idx : -1;
-}
-
-// The r-th item of workgroup slot (xcd, xj); -1 past its last one.  In a
-// mixed launch odd XCDs take their rounds from the last to the first: the
-// 256-row tiles, which come first, are bound by the matrix cores and the
-// smaller ones by HBM, so the two kinds run side by side instead of one after
-// the other (1999 tokens of the fine-grained layer: -4%; all but pure launches
-// of large tiles, which share weight bands between the XCDs: +2%).
-__device__ __forceinline__ int nth_item(const Sched& s, int r, int nwg, int xcd, int xj) {
-  if (!(xcd & 1) || !s.mixed) return round_item(s, r, nwg, xcd, xj);
-  const int nr = s.full + (round_item(s, s.full, nwg, xcd, xj) >= 0 ? 1 : 0);
-  return r < nr ? round_item(s, nr - 1 - r, nwg, xcd, xj) : -1;
-}
-
-// Pieces per tail tile: every combination of up to kMaxSplit pieces per
-// family is tried by one thread, which adds up the loads of a sample of
-// workgroups; the smallest maximum wins (fewest pieces on a tie).
-__device__ __forceinline__ void make_sched(Sched& s, const FfnParams& p, const_ptr<int32_t> tot, int nwg, int KT,
-                                           int* lds) {
-  const int tid = threadIdx.x;
-  s.b1 = uni(tot[0]);
-  s.b2 = s.b1 + uni(tot[1]);
-  s.total = s.b2 + uni(tot[2]);
-  const int rem = uni(s.total % nwg);
-  s.whole = s.total - rem;
-  s.items = s.total;
-  s.nsp = 0x111;
-  // nothing to gain: no tail, a small share of many rounds, K too short
-  if (rem == 0 || s.whole >= 8 * nwg || KT < 2 * kMinSplitSteps || p.split_slots == nullptr) return;
-  const int n[3] = {1 + (tid & 7), 1 + ((tid >> 3) & 7), 1 + (tid >> 6)};
-  bool ok = true;
-  int64_t floats = 0;
-  int c[3], end[3], items = s.whole;
-#pragma unroll
-  for (int f = 0; f < 3; ++f) {
-    const int tl = s.tail(f);
-    if (n[f] > 1 && (tl == 0 || KT < n[f] * kMinSplitSteps)) ok = false;
-    floats += (int64_t)tl * ((n[f] - 1) * fam_floats(f));
-    items += tl * n[f];
-    end[f] = items;
-    c[f] = piece_cost(f, KT, n[f]);
-  }
-  if (floats * 4 > p.split_bytes || items - s.whole > 4 * nwg) ok = false;
-  unsigned key = 0xffffffffu;
-  if (ok) {
-    int worst = 0;
-    // the round before the tail counts: its items may differ in size
-    const int base0 = max(0, s.whole - nwg);
-#pragma unroll
-    for (int q = 0; q < 5; ++q) {
-      const int lin = q * (nwg - 1) / 4;
-      int load = 0, at = lin;  // position within the round, reversed each time
-      for (int base = base0; base < items; base += nwg) {
-        const int it = base + at;
-        at = nwg - 1 - at;
-        load += it < s.whole ? step_cost(it < s.b1 ? 0 : it < s.b2 ? 1 : 2) * KT
-                : it < end[0] ? c[0] : it < end[1] ? c[1] : it < end[2] ? c[2] : 0;
-      }
-      worst = max(worst, load);
-    }
-    // smallest (cost, thread): lower thread ids have fewer pieces
-    key = (unsigned)min(worst, (1 << 22) - 1) * 512u + (unsigned)tid;
-  }
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) key = min(key, (unsigned)__shfl_xor((int)key, off));
-  if ((tid & 63) == 0) lds[tid >> 6] = (int)key;
-  __syncthreads();
-  unsigned best = 0xffffffffu;
-#pragma unroll
-  for (int w = 0; w < 8; ++w) best = min(best, (unsigned)lds[w]);
-  __syncthreads();
-  const int pick = uni(best == 0xffffffffu ? 0 : (int)(best & 511u));
-  s.nsp = (1 + (pick & 7)) | (1 + ((pick >> 3) & 7)) << 4 | (1 + (pick >> 6)) << 8;
-#pragma unroll
-  for (int f = 0; f < 3; ++f) s.items += s.tail(f) * (s.pieces(f) - 1);
 }
 
 // One work item: `rows` rows of a group from row y_row0 (h and y) / x_row0
@@ -855,10 +721,10 @@ __global__ __launch_bounds__(512, 2) void ffn_mfma_kernel(const FfnParams p) {
   const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_vptr)smem;
   const int nwg = gridDim.x;
   const int xcd = blockIdx.x & 7, xj = blockIdx.x >> 3;
+  const const_ptr<int32_t> tot = as_const(p.tile_totals);
   Sched sc;
-  make_sched(sc, p, as_const(p.tile_totals) + (GATED ? 0 : 3), nwg, p.K / kBK, reinterpret_cast<int*>(smem));
-  sc.full = uni(sc.items / nwg);
-  sc.mixed = sc.b1 > 0 && 6 * (sc.total - sc.b1) >= sc.b1;
+  sched_tiles(sc, uni(tot[0]), uni(tot[1]), uni(tot[2]), nwg);
+  sched_cut(sc, (unsigned)uni((int)*as_const(p.cut)), nwg);
   int r = 0;
   int item = nth_item(sc, r, nwg, xcd, xj);
   while (item >= 0) {
@@ -921,7 +787,7 @@ template <bool GATED>
 __global__ __launch_bounds__(256) void ffn_f32_kernel(const FfnParams p) {
   __shared__ float part[4][GATED ? 32 : 16][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int items = 4 * p.tile_totals[GATED ? 0 : 3];
+  const int items = 4 * p.tile_totals[0];
   const int K = p.K, n_out = p.n_out;
   const int r = lane & 31, h = lane >> 5;
 
@@ -973,25 +839,27 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const FfnParams p) {
   }
 }
 
-static int grid_for(int max_tiles, int cap) {
-  int g = max_tiles < cap ? max_tiles : cap;
-  g = (g + 7) & ~7;  // the XCD slot map needs a multiple of 8
-  return g < 8 ? 8 : g;
-}
-
 hipError_t launch_ffn(int stage, int act_dtype, int w_dtype, const GroupDesc* groups,
-                      const WeightDesc* wtab, int G, const int32_t* tile_totals,
-                      const int32_t* tile_group, float* split_slots, int32_t* split_cnt,
-                      int64_t split_bytes, int max_tiles,
+                      const WeightDesc* wtab, const int32_t* tile_totals, const int32_t* tile_group,
+                      float* split_slots, int32_t* split_cnt, int max_tiles,
                       const void* xp, void* h, void* y, int d, int f, int num_cu,
                       unsigned long long* clk, int clk_n, hipStream_t s) {
   if (max_tiles <= 0) return hipSuccess;
-  const FfnParams p = stage == 0 ? FfnParams{groups, wtab, tile_totals, tile_group, split_slots, split_cnt,
-                                             split_bytes, xp, h, G, d, f, clk, clk_n}
-                                 : FfnParams{groups, wtab, tile_totals, tile_group, split_slots, split_cnt,
-                                             split_bytes, h, y, G, f, d, clk, clk_n};
+  const FfnParams p{groups,
+                    wtab,
+                    tile_totals + 3 * stage,
+                    reinterpret_cast<const uint32_t*>(tile_totals) + kCutWord + stage,
+                    tile_group,
+                    split_slots,
+                    split_cnt,
+                    stage == 0 ? xp : h,
+                    stage == 0 ? h : y,
+                    stage == 0 ? d : f,
+                    stage == 0 ? f : d,
+                    clk,
+                    clk_n};
   if (act_dtype == 0) {
-    const int grid = grid_for(4 * std::min(max_tiles, 4 * num_cu), 8 * num_cu);
+    const int grid = std::min(4 * std::min(max_tiles, 4 * num_cu), 8 * num_cu);
     if (stage == 0)
       ffn_f32_kernel<true><<<grid, 256, 0, s>>>(p);
     else
@@ -1000,7 +868,7 @@ hipError_t launch_ffn(int stage, int act_dtype, int w_dtype, const GroupDesc* gr
   }
   // one 512-thread workgroup per CU; the tail of a launch is cut to fill the
   // whole grid, however few its tiles
-  const int grid = grid_for(num_cu, num_cu);
+  const int grid = ffn_grid(num_cu);
   if (w_dtype == 2) {
     if (stage == 0)
       ffn_mfma_kernel<true, true><<<grid, 512, 0, s>>>(p);

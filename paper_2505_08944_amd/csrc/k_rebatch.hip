@@ -20,7 +20,7 @@
 // copy every token's row in id order.
 #include <algorithm>
 
-#include "aep_internal.h"
+#include "ffn_sched.h"
 
 namespace aep {
 
@@ -125,6 +125,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(int E, int S, int n_
         tile_totals[f] = inc[1 + f] * nt0;
         tile_totals[3 + f] = inc[1 + f] * nt1;
       }
+      tile_totals[kCutWord] = tile_totals[kCutWord + 1] = (int32_t)kNoCut;
     }
     // The drained queues are empty again, in both halves of the depth
     // ping-pong: whichever half the next append reads starts from zero (so a
@@ -168,6 +169,25 @@ __device__ __forceinline__ void copy_pass(gsrc_t src, v4u* dst, int c0, int nchu
     if (FULL || c + 64 * i < nchunk) dst[c + 64 * i] = v[i];
 }
 
+// The cuts of both FFN launches' last rounds, chosen by kCutBlocks workgroups
+// in front of the gather's own: one thread per cut, the smallest word wins.
+// Beside the copies it costs the drain nothing; every FFN workgroup
+// working it out for itself took 1.0 us of each launch.
+constexpr int kCutBlocks = 4;
+static_assert(kCutBlocks * 256 == 2 * kCuts, "a thread per stage and cut");
+__device__ __forceinline__ void choose_cut(const CutArgs& a, int block) {
+  const int stage = block & 1, cut = (block >> 1) * 256 + (int)threadIdx.x;
+  Sched s;
+  sched_tiles(s, uni(a.tile_totals[3 * stage]), uni(a.tile_totals[3 * stage + 1]), uni(a.tile_totals[3 * stage + 2]),
+              a.nwg);
+  const int KT = stage == 0 ? a.kt[0] : a.kt[1];
+  if (!cut_pays(s, a.nwg, KT)) return;
+  uint32_t word = cut_word(s, a.nwg, KT, a.split_bytes, cut);
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) word = min(word, (uint32_t)__shfl_xor((int)word, off));
+  if ((threadIdx.x & 63) == 0) atomicMin(reinterpret_cast<uint32_t*>(a.tile_totals) + kCutWord + stage, word);
+}
+
 // LANES: E <= 64, an offset per lane.  57344 rows of 4 KB take 71 us, 3.3 TB/s
 // of stores beside as much read from the Infinity Cache (a row is read once
 // per selected expert); two or four rows per wave in flight took 72.
@@ -176,7 +196,12 @@ __global__ __launch_bounds__(256) void gather_kernel(
     const QEntry* __restrict__ q, int64_t q_stride, const int32_t* __restrict__ offsets, int E,
     int64_t N, int n_tokens, int shared, const void* const* __restrict__ tok_row, char* xp,
     int64_t row_bytes, int32_t* __restrict__ row_token, float* __restrict__ row_w,
-    int32_t* __restrict__ pos, float* __restrict__ posw, int k, int32_t* __restrict__ err) {
+    int32_t* __restrict__ pos, float* __restrict__ posw, int k, int32_t* __restrict__ err, const CutArgs cut) {
+  const int ncut = cut.nwg > 0 ? kCutBlocks : 0;
+  if ((int)blockIdx.x < ncut) {
+    choose_cut(cut, blockIdx.x);
+    return;
+  }
   __shared__ int32_t off_s[LANES ? 1 : kMaxGroups + 1];
   const int lane = threadIdx.x & 63;
   int my_off = 0;  // LANES: offsets[lane + 1], those past E equal to the last
@@ -186,7 +211,7 @@ __global__ __launch_bounds__(256) void gather_kernel(
     for (int i = threadIdx.x; i <= E; i += blockDim.x) off_s[i] = offsets[i];
     __syncthreads();
   }
-  const int64_t r = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t r = (int64_t)(blockIdx.x - ncut) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t R = N + (shared ? n_tokens : 0);
   if (r >= R) return;
   const int routed = LANES ? __builtin_amdgcn_readlane(my_off, 63) : off_s[E];
@@ -254,16 +279,16 @@ hipError_t launch_plan(int E, int S, int n_tokens, int k, int only_expert, int32
 hipError_t launch_gather(const QEntry* q, int64_t q_stride, const int32_t* offsets, int E,
                          int64_t N, int n_tokens, int shared, const void* const* tok_row,
                          char* xp, int64_t row_bytes, int32_t* row_token, float* row_w,
-                         int32_t* pos, float* posw, int k, int32_t* err, hipStream_t s) {
+                         int32_t* pos, float* posw, int k, int32_t* err, const CutArgs& cut, hipStream_t s) {
   const int64_t R = N + (shared ? n_tokens : 0);
   if (R == 0) return hipSuccess;
-  const int64_t nb = (R + 3) / 4;
+  const int64_t nb = (R + 3) / 4 + (cut.nwg > 0 ? kCutBlocks : 0);
   if (E <= 64)
     gather_kernel<true><<<(unsigned)nb, 256, 0, s>>>(q, q_stride, offsets, E, N, n_tokens, shared, tok_row, xp,
-                                                     row_bytes, row_token, row_w, pos, posw, k, err);
+                                                     row_bytes, row_token, row_w, pos, posw, k, err, cut);
   else
     gather_kernel<false><<<(unsigned)nb, 256, 0, s>>>(q, q_stride, offsets, E, N, n_tokens, shared, tok_row, xp,
-                                                      row_bytes, row_token, row_w, pos, posw, k, err);
+                                                      row_bytes, row_token, row_w, pos, posw, k, err, cut);
   return hipGetLastError();
 }
 

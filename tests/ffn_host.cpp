@@ -176,13 +176,9 @@ static long order_violations(int KT, const int* whole, bool tail, int arrival, i
     for (int f = 0; f < 3; ++f)
       if (f == 2 || (whole[1] + whole[2] == 0) || (f == 1 && whole[2] == 0)) tiles[f] += 4;
   for (int f = 0; f < 3; ++f) all += tiles[f];
-  sc.b1 = tiles[0];
-  sc.b2 = tiles[0] + tiles[1];
-  sc.total = all;
-  sc.whole = nwhole;
-  sc.nsp = tail ? 0x222 : 0x111;
-  sc.items = nwhole + 2 * (all - nwhole);
-  sc.full = sc.items / nwg;
+  sched_tiles(sc, tiles[0], tiles[1], tiles[2], nwg);
+  sc.whole = nwhole;  // (a tail of more than a round stays one)
+  sched_cut(sc, tail ? 1 << 6 | 1 << 3 | 1 : kNoCut, nwg);
   sc.mixed = mixed;
 
   // one group per 4 tiles: 4 columns of tiles, one row tile
@@ -251,6 +247,43 @@ static long order_violations(int KT, const int* whole, bool tail, int arrival, i
                    c * 16, a.wave, a.issue, a.done, w.wave, w.issue, w.done);
   }
   return bad;
+}
+
+// The cut of a launch of these tiles (pieces per family in bits 4f ..), chosen
+// as the device does.
+extern "C" int ffn_cut(int t0, int t1, int t2, int nwg, int KT, long split_bytes) {
+  Sched s;
+  sched_tiles(s, t0, t1, t2, nwg);
+  uint32_t word = kNoCut;
+  if (cut_pays(s, nwg, KT))
+    for (int cut = 0; cut < kCuts; ++cut) word = min(word, cut_word(s, nwg, KT, split_bytes, cut));
+  sched_cut(s, word, nwg);
+  return s.nsp;
+}
+
+// The largest cost of a workgroup in the last rounds under a cut (pieces per
+// family in bits 4f ..): every workgroup, item by item.  -1: a cut that is
+// not possible.
+extern "C" long ffn_cut_cost(int t0, int t1, int t2, int nwg, int KT, long split_bytes, int nsp) {
+  Sched s;
+  sched_tiles(s, t0, t1, t2, nwg);
+  long floats = 0, pieces = 0;
+  for (int f = 0; f < 3; ++f) {
+    const int n = (nsp >> (4 * f)) & 15;
+    if (n > 1 && (s.tail(f) == 0 || KT / n < kMinSplitSteps)) return -1;
+    floats += (long)s.tail(f) * (n - 1) * (kBM >> f) * kBN;
+    pieces += (long)s.tail(f) * n;
+  }
+  if (4 * floats > split_bytes || pieces > 4 * nwg) return -1;
+  s.nsp = nsp;
+  for (int f = 0; f < 3; ++f) s.items += s.tail(f) * (s.pieces(f) - 1);
+  const int base0 = max(0, s.whole - nwg);
+  std::vector<long> sum(nwg, 0);
+  for (int item = base0; item < s.items; ++item) {
+    const int f = item_family(s, item), r = (item - base0) / nwg, at = (item - base0) % nwg;
+    sum[r & 1 ? nwg - 1 - at : at] += item < s.whole ? step_cost(f) * KT : piece_cost(f, KT, s.pieces(f));
+  }
+  return *std::max_element(sum.begin(), sum.end());
 }
 
 extern "C" long ffn_order_violations(int gated, int fp8, int KT, const int* whole, int tail, int arrival, int xcd,

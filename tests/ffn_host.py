@@ -17,7 +17,7 @@ CLANG = "/opt/rocm/llvm/bin/clang++"
 def _device_part():
     """k_ffn.hip up to its host launchers, LDS accesses as recorder calls."""
     src = open(os.path.join(CSRC, "k_ffn.hip")).read()
-    head, rest = src.split("static int grid_for(", 1)
+    head, rest = src.split("hipError_t launch_ffn(", 1)
     assert "<<<" not in head and "<<<" in rest
 
     def sub(pattern, repl, text, n, flags=0):
