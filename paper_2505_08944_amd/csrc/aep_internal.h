@@ -156,6 +156,7 @@ struct CutArgs {
   int32_t* tile_totals;
   int nwg;              // workgroups of the FFN launches
   int kt[2];            // K steps per stage
+  bool fp8;             // fp8 weights
   int64_t split_bytes;  // room for partial sums
 };
 hipError_t launch_gather(const QEntry* q, int64_t q_stride, const int32_t* offsets, int E,

@@ -130,6 +130,7 @@ CutArgs cut_args(Ctx& c) {
   return CutArgs{c.at<int32_t>(c.off_tiles),
                  c.cfg.act_dtype == AEP_F32 ? 0 : ffn_grid(c.num_cu),
                  {c.cfg.d_model / kBK, c.cfg.d_ffn / kBK},
+                 c.cfg.w_dtype == AEP_FP8_E4M3,
                  (int64_t)c.split_bytes};
 }
 

@@ -84,12 +84,22 @@ constexpr int kCuts = 1 << (3 * kCutBits);
 static_assert(kMaxSplit == 1 << kCutBits, "pieces of a tile in kCutBits bits");
 __device__ __forceinline__ int cut_pieces(int cut, int f) { return 1 + ((cut >> (kCutBits * f)) & (kMaxSplit - 1)); }
 
-// Relative cost of one K step of a tile per family: a 256-row step is bound
-// by its MFMAs, the smaller ones by the CU's load path (64, 48 and 40 KB per
-// step), and the cost of a split tile's partial sums in the same unit.
-__device__ __forceinline__ int step_cost(int f) { return f == 0 ? 8 : f == 1 ? 6 : 5; }
-__device__ __forceinline__ int piece_cost(int f, int KT, int n) {
-  return step_cost(f) * KT / n + (n > 1 ? (40 + 20 * n) >> f : 0);
+// Relative cost of one K step of a tile, and of adding the partial sums of n
+// pieces, about 0.1 us each.  16 experts of 256, 128, 64 and 16 rows (d = 4096,
+// f = 2048, gate/up, one tile per CU, weights in HBM) took 117, 110, 105 and
+// 106 us with bf16 weights, whose streaming bounds all heights alike when
+// every CU does it, and 113, 78, 63 and 56 with fp8, whose half as many bytes
+// leave a 256-row step to its MFMAs and the widening.  Adding 2 to 8 pieces
+// took 17 to 45 us in 256-row tiles and 10 to 28 in 64-row ones.  With these
+// constants the cuts chosen for 54 bf16 and 26 fp8 launches, each timed under
+// all cuts worth trying, were 0.5% and 0.2% slower than the best on average
+// (with one set of constants for both formats, in the ratio of the bf16 bytes
+// per step, 0.8% and 0.6%, and up to 11%).
+__device__ __forceinline__ int step_cost(bool fp8, int f) {
+  return f == 0 ? 16 : fp8 ? (f == 1 ? 11 : 8) : (f == 1 ? 13 : 9);
+}
+__device__ __forceinline__ int piece_cost(bool fp8, int f, int KT, int n) {
+  return step_cost(fp8, f) * KT / n + (n > 1 ? (30 + 10 * n) * (4 - f) : 0);
 }
 __device__ __forceinline__ int fam_floats(int f) { return (kBM * kBN) >> f; }
 
@@ -98,13 +108,13 @@ __device__ __forceinline__ int fam_floats(int f) { return (kBM * kBN) >> f; }
 // the order in which they are dealt.  A workgroup's sum changes only where one
 // of its rounds passes from one kind of item to the next, so the slots that
 // follow such a passage, and slot 0, stand for all.
-__device__ __forceinline__ int cut_time(const Sched& s, int nwg, int KT, const int (&n)[3]) {
+__device__ __forceinline__ int cut_time(const Sched& s, bool fp8, int nwg, int KT, const int (&n)[3]) {
   int end[3], c[3], items = s.whole;
 #pragma unroll
   for (int f = 0; f < 3; ++f) {
     items += s.tail(f) * n[f];
     end[f] = items;
-    c[f] = piece_cost(f, KT, n[f]);
+    c[f] = piece_cost(fp8, f, KT, n[f]);
   }
   const int base0 = max(0, s.whole - nwg);
   const int w0 = min(s.b1, s.whole), w1 = min(s.b2, s.whole);
@@ -113,7 +123,9 @@ __device__ __forceinline__ int cut_time(const Sched& s, int nwg, int KT, const i
     for (int base = base0; base < items; base += nwg) {
       const int it = base + at;
       at = nwg - 1 - at;  // the next round is reversed
-      sum += it < w0 ? step_cost(0) * KT : it < w1 ? step_cost(1) * KT : it < s.whole ? step_cost(2) * KT
+      sum += it < w0        ? step_cost(fp8, 0) * KT
+             : it < w1      ? step_cost(fp8, 1) * KT
+             : it < s.whole ? step_cost(fp8, 2) * KT
              : it < end[0] ? c[0] : it < end[1] ? c[1] : it < end[2] ? c[2] : 0;
     }
     return sum;
@@ -133,7 +145,8 @@ __device__ __forceinline__ int cut_time(const Sched& s, int nwg, int KT, const i
 // (time, cut) in one word: the smallest word is the cut to take, the fewest
 // pieces where times are equal.  ~0: not possible.
 constexpr uint32_t kNoCut = 0xffffffffu;
-__device__ __forceinline__ uint32_t cut_word(const Sched& s, int nwg, int KT, int64_t split_bytes, int cut) {
+__device__ __forceinline__ uint32_t cut_word(const Sched& s, bool fp8, int nwg, int KT, int64_t split_bytes,
+                                             int cut) {
   const int n[3] = {cut_pieces(cut, 0), cut_pieces(cut, 1), cut_pieces(cut, 2)};
   int64_t floats = 0;
   int items = 0;
@@ -145,7 +158,7 @@ __device__ __forceinline__ uint32_t cut_word(const Sched& s, int nwg, int KT, in
     items += tl * n[f];
   }
   if (floats * 4 > split_bytes || items > 4 * nwg) return kNoCut;
-  return (uint32_t)min(cut_time(s, nwg, KT, n), (1 << (32 - 3 * kCutBits)) - 2) * kCuts + (uint32_t)cut;
+  return (uint32_t)min(cut_time(s, fp8, nwg, KT, n), (1 << (32 - 3 * kCutBits)) - 2) * kCuts + (uint32_t)cut;
 }
 // Nothing to gain: no tail, a small share of many rounds, K too short.
 __device__ __forceinline__ bool cut_pays(const Sched& s, int nwg, int KT) {

@@ -182,7 +182,7 @@ __device__ __forceinline__ void choose_cut(const CutArgs& a, int block) {
               a.nwg);
   const int KT = stage == 0 ? a.kt[0] : a.kt[1];
   if (!cut_pays(s, a.nwg, KT)) return;
-  uint32_t word = cut_word(s, a.nwg, KT, a.split_bytes, cut);
+  uint32_t word = cut_word(s, a.fp8, a.nwg, KT, a.split_bytes, cut);
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) word = min(word, (uint32_t)__shfl_xor((int)word, off));
   if ((threadIdx.x & 63) == 0) atomicMin(reinterpret_cast<uint32_t*>(a.tile_totals) + kCutWord + stage, word);

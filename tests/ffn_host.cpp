@@ -251,12 +251,12 @@ static long order_violations(int KT, const int* whole, bool tail, int arrival, i
 
 // The cut of a launch of these tiles (pieces per family in bits 4f ..), chosen
 // as the device does.
-extern "C" int ffn_cut(int t0, int t1, int t2, int nwg, int KT, long split_bytes) {
+extern "C" int ffn_cut(int fp8, int t0, int t1, int t2, int nwg, int KT, long split_bytes) {
   Sched s;
   sched_tiles(s, t0, t1, t2, nwg);
   uint32_t word = kNoCut;
   if (cut_pays(s, nwg, KT))
-    for (int cut = 0; cut < kCuts; ++cut) word = min(word, cut_word(s, nwg, KT, split_bytes, cut));
+    for (int cut = 0; cut < kCuts; ++cut) word = min(word, cut_word(s, fp8, nwg, KT, split_bytes, cut));
   sched_cut(s, word, nwg);
   return s.nsp;
 }
@@ -264,7 +264,7 @@ extern "C" int ffn_cut(int t0, int t1, int t2, int nwg, int KT, long split_bytes
 // The largest cost of a workgroup in the last rounds under a cut (pieces per
 // family in bits 4f ..): every workgroup, item by item.  -1: a cut that is
 // not possible.
-extern "C" long ffn_cut_cost(int t0, int t1, int t2, int nwg, int KT, long split_bytes, int nsp) {
+extern "C" long ffn_cut_cost(int fp8, int t0, int t1, int t2, int nwg, int KT, long split_bytes, int nsp) {
   Sched s;
   sched_tiles(s, t0, t1, t2, nwg);
   long floats = 0, pieces = 0;
@@ -281,7 +281,7 @@ extern "C" long ffn_cut_cost(int t0, int t1, int t2, int nwg, int KT, long split
   std::vector<long> sum(nwg, 0);
   for (int item = base0; item < s.items; ++item) {
     const int f = item_family(s, item), r = (item - base0) / nwg, at = (item - base0) % nwg;
-    sum[r & 1 ? nwg - 1 - at : at] += item < s.whole ? step_cost(f) * KT : piece_cost(f, KT, s.pieces(f));
+    sum[r & 1 ? nwg - 1 - at : at] += item < s.whole ? step_cost(fp8, f) * KT : piece_cost(fp8, f, KT, s.pieces(f));
   }
   return *std::max_element(sum.begin(), sum.end());
 }
