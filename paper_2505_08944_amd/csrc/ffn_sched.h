@@ -4,9 +4,10 @@
 //
 // Tiles are numbered family by family (256, 128, 64 rows).  The first
 // `whole` of them -- full rounds of the grid -- are one work item each.  The
-// others, a partial round, would leave CUs idle: they are cut along K into
-// nsp[family] pieces (at least kMinSplitSteps steps each), whose f32 partial
-// sums meet in the workspace.  Items are dealt round by round; odd rounds in
+// others, a partial round, would leave CUs idle: they are cut, either all into
+// column halves or not, and then along K into nsp[family] pieces (at least
+// kMinSplitSteps steps each), whose f32 partial sums meet in the workspace.
+// Halves need no sums, but read the rows twice.  Items are dealt round by round; odd rounds in
 // reverse, so that a workgroup that got one of a round's larger items gets
 // one of the next round's smaller ones.
 #pragma once
@@ -23,12 +24,14 @@ struct Sched {
   int whole, items;
   int full;           // full rounds of items
   bool mixed;         // 256-row tiles beside a sixth as many smaller ones or more
-  int nsp;            // pieces per tail tile: family f in bits 4f .. 4f + 3
+  int halves;         // 2: tail tiles are cut into column halves, 1: not
+  int nsp;            // pieces per tail tile or half: family f in bits 4f .. 4f + 3
   __device__ __forceinline__ int first(int f) const { return f == 0 ? 0 : f == 1 ? b1 : f == 2 ? b2 : total; }
   // first tail tile of family f and how many there are
   __device__ __forceinline__ int tail0(int f) const { return max(first(f), whole); }
   __device__ __forceinline__ int tail(int f) const { return max(0, first(f + 1) - tail0(f)); }
   __device__ __forceinline__ int pieces(int f) const { return (nsp >> (4 * f)) & 15; }
+  __device__ __forceinline__ int tail_items(int f) const { return tail(f) * halves * pieces(f); }
 };
 
 __device__ __forceinline__ void sched_tiles(Sched& s, int t0, int t1, int t2, int nwg) {
@@ -37,6 +40,7 @@ __device__ __forceinline__ void sched_tiles(Sched& s, int t0, int t1, int t2, in
   s.total = s.b2 + t2;
   s.whole = s.total - uni(s.total % nwg);
   s.items = s.total;
+  s.halves = 1;
   s.nsp = 0x111;
 }
 
@@ -44,8 +48,12 @@ __device__ __forceinline__ void sched_tiles(Sched& s, int t0, int t1, int t2, in
 __device__ __forceinline__ int item_family(const Sched& s, int item) {
   if (item < s.whole) return item < s.b1 ? 0 : (item < s.b2 ? 1 : 2);
   const int j = item - s.whole;
-  const int m0 = s.tail(0) * s.pieces(0), m1 = s.tail(1) * s.pieces(1);
+  const int m0 = s.tail_items(0), m1 = s.tail_items(1);
   return j < m0 ? 0 : (j < m0 + m1 ? 1 : 2);
+}
+// Items of one kind have one tile shape: family and, in bit 2, column halves.
+__device__ __forceinline__ int item_kind(const Sched& s, int item) {
+  return item_family(s, item) | (item >= s.whole && s.halves == 2 ? 4 : 0);
 }
 
 // Work item of workgroup slot lin (XCD-blocked: lin / (nwg / 8) is its XCD)
@@ -78,55 +86,74 @@ __device__ __forceinline__ int nth_item(const Sched& s, int r, int nwg, int xcd,
 }
 
 // -------------------------------------------------- cutting the last round
-// A cut is a number below kCuts: pieces - 1 of family f in bits 3f .. 3f + 2.
+// A cut is a number below kCuts: pieces - 1 of family f in bits 3f .. 3f + 2,
+// column halves in bit 9.
 constexpr int kCutBits = 3;
-constexpr int kCuts = 1 << (3 * kCutBits);
+constexpr int kCuts = 2 << (3 * kCutBits);
 static_assert(kMaxSplit == 1 << kCutBits, "pieces of a tile in kCutBits bits");
 __device__ __forceinline__ int cut_pieces(int cut, int f) { return 1 + ((cut >> (kCutBits * f)) & (kMaxSplit - 1)); }
+__device__ __forceinline__ int cut_halves(int cut) { return 1 + (cut >> (3 * kCutBits)); }
 
-// Relative cost of one K step of a tile, and of adding the partial sums of n
-// pieces, about 0.1 us each.  16 experts of 256, 128, 64 and 16 rows (d = 4096,
-// f = 2048, gate/up, one tile per CU, weights in HBM) took 117, 110, 105 and
-// 106 us with bf16 weights, whose streaming bounds all heights alike when
-// every CU does it, and 113, 78, 63 and 56 with fp8, whose half as many bytes
-// leave a 256-row step to its MFMAs and the widening.  Adding 2 to 8 pieces
-// took 17 to 45 us in 256-row tiles and 10 to 28 in 64-row ones.  With these
-// constants the cuts chosen for 54 bf16 and 26 fp8 launches, each timed under
-// all cuts worth trying, were 0.5% and 0.2% slower than the best on average
-// (with one set of constants for both formats, in the ratio of the bf16 bytes
-// per step, 0.8% and 0.6%, and up to 11%).
-__device__ __forceinline__ int step_cost(bool fp8, int f) {
-  return f == 0 ? 16 : fp8 ? (f == 1 ? 11 : 8) : (f == 1 ? 13 : 9);
+// Time of one K step of a tile or half, and of adding the sums of n pieces, in
+// units of 0.01 us.  A step takes longer the more CUs stream weights beside it:
+// from the first value, with few of them, to the second, with all.  With the
+// weights in HBM, d = 4096, f = 2048, gate/up, a tile per CU: 16 experts of
+// 256, 128 and 64 rows 117, 110 and 105 us with bf16 weights, whose streaming
+// bounds all heights alike, and 113, 78 and 63 with fp8, whose half as many
+// bytes leave a 256-row step to its MFMAs and the widening; 8 experts in halves
+// 73, 58 and 55 (fp8 74, 53 and 43), in two pieces of whole tiles 86, 66 and 63
+// (76, 51, 44).  Adding 2 to 8 pieces took 17 to 45 us in 256-row tiles and 10
+// to 28 in 64-row ones.  The cuts that these constants choose for 844 launches
+// of 1 to 32 experts, each timed under all cuts worth trying, were 0.9% slower
+// than the best on average.
+__device__ __forceinline__ int step_time(bool fp8, int f, int halves, int busy, int nwg) {
+  const int lo = fp8 ? (halves == 1 ? (f == 0 ? 165 : f == 1 ? 70 : 60) : (f == 0 ? 85 : f == 1 ? 65 : 45))
+                     : (halves == 1 ? (f == 0 ? 75 : f == 1 ? 70 : 60) : (f == 0 ? 60 : f == 1 ? 45 : 35));
+  const int hi = fp8 ? (halves == 1 ? (f == 0 ? 165 : f == 1 ? 100 : 90) : (f == 0 ? 100 : f == 1 ? 65 : 50))
+                     : (halves == 1 ? (f == 0 ? 175 : f == 1 ? 150 : 145) : (f == 0 ? 105 : f == 1 ? 80 : 75));
+  return lo + (hi - lo) * busy / nwg;
 }
-__device__ __forceinline__ int piece_cost(bool fp8, int f, int KT, int n) {
-  return step_cost(fp8, f) * KT / n + (n > 1 ? (30 + 10 * n) * (4 - f) : 0);
+__device__ __forceinline__ int piece_time(bool fp8, int f, int halves, int KT, int n, int busy, int nwg) {
+  const int sums = f == 0 ? 515 + 325 * n : f == 1 ? 420 + 270 * n : 335 + 195 * n;
+  return step_time(fp8, f, halves, busy, nwg) * KT / n + (n == 1 ? 0 : halves == 1 ? sums : sums * 4 / 5);
 }
-__device__ __forceinline__ int fam_floats(int f) { return (kBM * kBN) >> f; }
+// f32 values of one piece's sums
+__device__ __forceinline__ int part_floats(int f, int halves) { return ((kBM * kBN) >> f) / halves; }
 
 // The time of the last rounds under a cut: the largest sum of one workgroup's
 // items, from the round before the tail on (its items may differ in size), in
 // the order in which they are dealt.  A workgroup's sum changes only where one
 // of its rounds passes from one kind of item to the next, so the slots that
 // follow such a passage, and slot 0, stand for all.
-__device__ __forceinline__ int cut_time(const Sched& s, bool fp8, int nwg, int KT, const int (&n)[3]) {
-  int end[3], c[3], items = s.whole;
+__device__ __forceinline__ int cut_time(const Sched& s, bool fp8, int nwg, int KT, int halves, const int (&n)[3]) {
+  int end[3], items = s.whole;
 #pragma unroll
   for (int f = 0; f < 3; ++f) {
-    items += s.tail(f) * n[f];
+    items += s.tail(f) * halves * n[f];
     end[f] = items;
-    c[f] = piece_cost(fp8, f, KT, n[f]);
   }
-  const int base0 = max(0, s.whole - nwg);
+  const int base0 = max(0, s.whole - nwg), last = (items - 1) / nwg * nwg;
+  int w[3], c[3], cl[3];  // a whole tile; an item of the tail, in a full round and in the last
+#pragma unroll
+  for (int f = 0; f < 3; ++f) {
+    w[f] = piece_time(fp8, f, 1, KT, 1, nwg, nwg);
+    c[f] = piece_time(fp8, f, halves, KT, n[f], nwg, nwg);
+    cl[f] = piece_time(fp8, f, halves, KT, n[f], items - last, nwg);
+  }
   const int w0 = min(s.b1, s.whole), w1 = min(s.b2, s.whole);
   auto load = [&](int lin) {
     int sum = 0, at = lin;
     for (int base = base0; base < items; base += nwg) {
       const int it = base + at;
       at = nwg - 1 - at;  // the next round is reversed
-      sum += it < w0        ? step_cost(fp8, 0) * KT
-             : it < w1      ? step_cost(fp8, 1) * KT
-             : it < s.whole ? step_cost(fp8, 2) * KT
-             : it < end[0] ? c[0] : it < end[1] ? c[1] : it < end[2] ? c[2] : 0;
+      if (it < s.whole)
+        sum += it < w0 ? w[0] : it < w1 ? w[1] : w[2];
+      else if (it < end[0])
+        sum += base == last ? cl[0] : c[0];
+      else if (it < end[1])
+        sum += base == last ? cl[1] : c[1];
+      else if (it < end[2])
+        sum += base == last ? cl[2] : c[2];
     }
     return sum;
   };
@@ -147,31 +174,31 @@ __device__ __forceinline__ int cut_time(const Sched& s, bool fp8, int nwg, int K
 constexpr uint32_t kNoCut = 0xffffffffu;
 __device__ __forceinline__ uint32_t cut_word(const Sched& s, bool fp8, int nwg, int KT, int64_t split_bytes,
                                              int cut) {
-  const int n[3] = {cut_pieces(cut, 0), cut_pieces(cut, 1), cut_pieces(cut, 2)};
+  const int n[3] = {cut_pieces(cut, 0), cut_pieces(cut, 1), cut_pieces(cut, 2)}, halves = cut_halves(cut);
   int64_t floats = 0;
   int items = 0;
 #pragma unroll
   for (int f = 0; f < 3; ++f) {
-    const int tl = s.tail(f);
+    const int tl = s.tail(f) * halves;
     if (n[f] > 1 && (tl == 0 || KT < n[f] * kMinSplitSteps)) return kNoCut;
-    floats += (int64_t)tl * ((n[f] - 1) * fam_floats(f));
+    floats += (int64_t)tl * ((n[f] - 1) * part_floats(f, halves));
     items += tl * n[f];
   }
   if (floats * 4 > split_bytes || items > 4 * nwg) return kNoCut;
-  return (uint32_t)min(cut_time(s, fp8, nwg, KT, n), (1 << (32 - 3 * kCutBits)) - 2) * kCuts + (uint32_t)cut;
+  return (uint32_t)min(cut_time(s, fp8, nwg, KT, halves, n), (1 << (31 - 3 * kCutBits)) - 2) * kCuts + (uint32_t)cut;
 }
-// Nothing to gain: no tail, a small share of many rounds, K too short.
-__device__ __forceinline__ bool cut_pays(const Sched& s, int nwg, int KT) {
-  return s.whole != s.total && s.whole < 8 * nwg && KT >= 2 * kMinSplitSteps;
+// Something to gain: a tail, and no small share of many rounds.  (And a counter
+// for each half of up to nwg - 1 tiles.)
+__device__ __forceinline__ bool cut_pays(const Sched& s, int nwg) {
+  return s.whole != s.total && s.whole < 8 * nwg && 2 * nwg <= kSplitCounters;
 }
 
 // Takes the cut of a word (kNoCut: none) and settles the rounds.
 __device__ __forceinline__ void sched_cut(Sched& s, uint32_t word, int nwg) {
   const int cut = word == kNoCut ? 0 : (int)(word % kCuts);
+  s.halves = cut_halves(cut);
   s.nsp = cut_pieces(cut, 0) | cut_pieces(cut, 1) << 4 | cut_pieces(cut, 2) << 8;
-  s.items = s.total;
-#pragma unroll
-  for (int f = 0; f < 3; ++f) s.items += s.tail(f) * (s.pieces(f) - 1);
+  s.items = s.whole + s.tail_items(0) + s.tail_items(1) + s.tail_items(2);
   s.full = uni(s.items / nwg);
   s.mixed = s.b1 > 0 && 6 * (s.total - s.b1) >= s.b1;
 }

@@ -10,7 +10,8 @@
 // 256-row tiles and one remainder tile of the smallest height that holds the
 // rest, so an expert's weights are read ceil(rows / 256) times.  It lays the
 // tiles of all groups end to end, family by family; this kernel deals them to
-// the workgroups (see Sched).
+// the workgroups, those of the last, partial round in column halves, K pieces
+// or both (ffn_sched.h).
 //
 // Ping-pong.  The eight waves form two groups of four; a SIMD runs one wave
 // of each.  A workgroup barrier ends every slot, and in a slot one group
@@ -145,34 +146,36 @@ struct Item {
 };
 // Where a tail tile's item stands among its pieces.
 struct Piece {
-  int n, piece, cnt;  // pieces, this one, the tile's counter
-  int64_t slot;       // float offset of the tile's partial sums
-  int tile;
+  int n, piece, cnt;  // pieces, this one, their counter
+  int64_t slot;       // float offset of their partial sums
+  int tile, half;     // half: column half of the tile (0 if it is not cut)
 };
 
 __device__ __forceinline__ Piece decode_piece(const Sched& s, int item, int f) {
-  Piece q{1, 0, 0, 0, item};
+  Piece q{1, 0, 0, 0, item, 0};
   if (item < s.whole) return q;
   int j = item - s.whole;
   int64_t slot = 0;
 #pragma unroll
   for (int e = 0; e < 2; ++e)
     if (f > e) {
-      j -= s.tail(e) * s.pieces(e);
-      q.cnt += s.tail(e);
-      slot += (int64_t)s.tail(e) * (s.pieces(e) - 1) * fam_floats(e);
+      j -= s.tail_items(e);
+      q.cnt += s.tail(e) * s.halves;
+      slot += (int64_t)s.tail(e) * s.halves * (s.pieces(e) - 1) * part_floats(e, s.halves);
     }
   q.n = s.pieces(f);
   const int ti = q.n == 1 ? j : uni(j / q.n);
   q.piece = j - ti * q.n;
-  q.tile = s.tail0(f) + ti;
+  q.tile = s.tail0(f) + (s.halves == 2 ? ti >> 1 : ti);
+  q.half = s.halves == 2 ? ti & 1 : 0;
   q.cnt += ti;
-  q.slot = slot + (int64_t)ti * (q.n - 1) * fam_floats(f);
+  q.slot = slot + (int64_t)ti * (q.n - 1) * part_floats(f, s.halves);
   return q;
 }
 
-template <bool GATED>
-__device__ __forceinline__ Item decode_item(const FfnParams& p, const Sched& s, int item, int f, int ncol, int KT) {
+template <bool GATED, int FAM, int NB>
+__device__ __forceinline__ Item decode_item(const FfnParams& p, const Sched& s, int item, int ncol, int KT) {
+  constexpr int f = FAM;
   const Piece q = decode_piece(s, item, f);
   Item it;
   it.k0 = q.n == 1 ? 0 : uni(q.piece * KT / q.n);
@@ -185,17 +188,21 @@ __device__ __forceinline__ Item decode_item(const FfnParams& p, const Sched& s, 
     int rt;
     panel_decode<GATED ? 8 : 4>(local, gd->nrt[0], ncol, rt, it.nti);
     m0 = rt * kBM;
-    it.rot = 0;
   } else {
     it.nti = local;
     m0 = gd->row1;
+  }
+  if (f == 0 && NB == 2) {
+    it.rot = 0;
+  } else {
     // Smaller tiles stream weights: tiles that run together start their K
     // walk at different steps, so they do not read the same DRAM channels
     // in lockstep (a load-only probe: 0.68 -> 0.79 of peak bandwidth).
     // 256-row tiles share bands with their neighbours in an XCD's L2, which
     // a rotation would pull apart.
-    it.rot = uni((int)((7u * (unsigned)q.tile) % (unsigned)it.kn));
+    it.rot = uni((int)((7u * (unsigned)(q.tile + q.half)) % (unsigned)it.kn));
   }
+  if (NB == 1) it.nti = 2 * it.nti + q.half;
   it.rows = uni(gd->n - m0);
   it.x_row0 = uni(gd->x_row0 + m0);
   it.y_row0 = uni(gd->y_row0 + m0);
@@ -205,24 +212,28 @@ __device__ __forceinline__ Item decode_item(const FfnParams& p, const Sched& s, 
 
 // ------------------------------------------------------------- tile families
 // A K step's LDS stage holds the A rows (128 bytes each) in units of up to
-// 128 rows, then two B units of 128 rows (128 bytes each, 64 for fp8).  B
-// unit b, rows 32w .. 32w + 31 belong to wave column w: gate/up: 16 gate
-// features and the same 16 up features (tile features 32w + 16b ...), so a
-// lane holds both accumulators of an output; down: 32 output columns.
+// 128 rows (256 where there is one B unit), then NB B units of 128 rows (128
+// bytes each, 64 for fp8): two in a whole tile, one in a column half.  B unit
+// b, rows 32w .. 32w + 31 belong to wave column w: gate/up: 16 gate features
+// and the same 16 up features (tile features 16 NB w + 16 b ...), so a lane
+// holds both accumulators of an output; down: 32 output columns.
 // 16-byte chunk c of row r sits at position c ^ (r % 8) (fp8 B rows: c ^
 // ((r / 4) % 4)), which spreads the rows one read covers over the banks; the
 // loader lanes fetch the chunk that belongs at their fixed LDS position.
-template <bool FP8, int FAM>
+template <bool FP8, int FAM, int NB>
 struct Fam {
   static constexpr int kRows = kBM >> FAM;
-  static constexpr int kUnits = FAM == 0 ? 2 : 1;        // A units per stage
-  static constexpr int kUnitRows = kRows / kUnits;       // 128, 128, 64
+  static constexpr bool kFour = FAM == 0 && NB == 2;     // four phases per K step, else one
+  static constexpr int kUnits = kFour ? 2 : 1;           // A units per stage
+  static constexpr int kUnitRows = kRows / kUnits;       // 128, 128, 64; of halves 256, 128, 64
   static constexpr int RF = kUnitRows / 32;              // 16-row fragments per wave and unit
   static constexpr int kA = kUnitRows * 128;             // bytes of an A unit
   static constexpr int kB = 128 * (FP8 ? 64 : 128);      // bytes of a B unit
-  static constexpr int kStage = kUnits * kA + 2 * kB;
+  static constexpr int kStage = kUnits * kA + NB * kB;
   // ring depth: what fits 160 KB
-  static constexpr int kStages = FAM == 0 ? (FP8 ? 3 : 2) : FAM == 1 ? (FP8 ? 5 : 3) : (FP8 ? 6 : 4);
+  static constexpr int kStages = NB == 2 ? (FAM == 0 ? (FP8 ? 3 : 2) : FAM == 1 ? (FP8 ? 5 : 3) : (FP8 ? 6 : 4))
+                                         : (FAM == 0 ? (FP8 ? 4 : 3) : FAM == 1 ? (FP8 ? 6 : 5) : (FP8 ? 8 : 6));
+  static constexpr int kCols = kBN / 2 * NB;             // B rows: output columns, or gate and up features
   static constexpr int kLA = kUnitRows / 64;             // loads per wave: an A unit
   static constexpr int kLB = FP8 ? 1 : 2;                // ... and a B unit
   static_assert(kStages * kStage <= kFfnLds, "the ring fits the LDS");
@@ -239,7 +250,7 @@ struct Stream {
   }
 };
 
-template <bool GATED, bool FP8, int FAM>
+template <bool GATED, bool FP8, int FAM, int NB>
 __device__ __forceinline__ void stream_set(Stream& st, const FfnParams& p, const Item& it, int wave) {
   const int K = p.K;
   const const_ptr<WeightDesc> wd = as_const(p.wtab) + it.g;
@@ -247,10 +258,11 @@ __device__ __forceinline__ void stream_set(Stream& st, const FfnParams& p, const
   // rows past the group's end and columns past the matrix are out of the
   // resources' range: they read as zeros, cost no traffic, and their outputs
   // are not stored
-  st.a = make_rsrc(a, (uint32_t)min(it.rows, Fam<FP8, FAM>::kRows) * (uint32_t)K * 2u);
+  st.a = make_rsrc(a, (uint32_t)min(it.rows, Fam<FP8, FAM, NB>::kRows) * (uint32_t)K * 2u);
   const unsigned char* w =
       reinterpret_cast<const unsigned char*>(GATED ? ((wave & 1) ? wd->up : wd->gate) : wd->down);
-  const int c0 = it.nti * (GATED ? kBN / 2 : kBN);
+  // (the second half of the last tile may lie past the matrix)
+  const int c0 = min(it.nti * (Fam<FP8, FAM, NB>::kCols / (GATED ? 2 : 1)), p.n_out);
   constexpr uint32_t esz = FP8 ? 1u : 2u;
   st.b = make_rsrc(w + (int64_t)c0 * K * esz, (uint32_t)(p.n_out - c0) * (uint32_t)K * esz);
   st.k0 = it.k0;
@@ -267,13 +279,15 @@ __device__ __forceinline__ void stream_null(Stream& st) {
   st.left = INT_MAX;
 }
 
-// Runs the chain of items of family FAM that starts at round r of this
-// workgroup (whose item is `item`); leaves r and item at the first one of
-// another family (item < 0: none left).
-template <bool GATED, bool FP8, int FAM>
+// Runs the chain of items of family FAM and NB B units that starts at round r
+// of this workgroup (whose item is `item`); leaves r and item at the first one
+// of another kind (item < 0: none left).
+template <bool GATED, bool FP8, int FAM, int NB>
 __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, unsigned char* smem,
                                            uint32_t lds_base, int nwg, int xcd, int xj, int& r, int& item) {
-  using F = Fam<FP8, FAM>;
+  using F = Fam<FP8, FAM, NB>;
+  constexpr bool kFour = F::kFour;
+  constexpr int kOut = F::kCols / (GATED ? 2 : 1);  // output columns of an item
   constexpr int RF = F::RF, NU = F::kUnits, NST = F::kStages;
   int tid = threadIdx.x;
   // per-lane offsets are recomputed here instead of being kept live across
@@ -286,7 +300,7 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
   const int ncol = (n_out + (GATED ? kBN / 2 : kBN) - 1) / (GATED ? kBN / 2 : kBN);
 
   // loader offsets: the same for every tile (the resources move)
-  uint32_t aoff[NU][F::kLA], boff[2][F::kLB];
+  uint32_t aoff[NU][F::kLA], boff[NB][F::kLB];
 #pragma unroll
   for (int u = 0; u < NU; ++u)
 #pragma unroll
@@ -295,12 +309,12 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
       aoff[u][i] = (uint32_t)(u * 128 + row) * (uint32_t)K * 2u + (uint32_t)(((lane & 7) ^ (lane >> 3)) << 4);
     }
 #pragma unroll
-  for (int b = 0; b < 2; ++b)
+  for (int b = 0; b < NB; ++b)
 #pragma unroll
     for (int i = 0; i < F::kLB; ++i) {
       const int lr = wave * 16 + (FP8 ? (lane >> 2) : i * 8 + (lane >> 3));
       const int c = FP8 ? ((lane & 3) ^ ((lr >> 2) & 3)) : ((lane & 7) ^ (lr & 7));
-      const int col = GATED ? (wave >> 1) * 32 + b * 16 + (lr & 15) : b * 128 + lr;
+      const int col = GATED ? (wave >> 1) * (16 * NB) + b * 16 + (lr & 15) : b * 128 + lr;
       boff[b][i] = (uint32_t)col * (uint32_t)K * (FP8 ? 1u : 2u) + (uint32_t)(c << 4);
     }
   const uint32_t la = lds_base + wave * (F::kLA * 1024), lb = lds_base + NU * F::kA + wave * (F::kLB * 1024);
@@ -321,12 +335,12 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
   // fragment][column fragment]: rows of the MFMA result are columns of the
   // output, so a lane holds four consecutive output columns of one row.
   // rn: a B unit as read; it becomes rb[b] in widen(b) -- for fp8 weights by
-  // the exact conversion of its bytes, and in family 0 for B unit 0 because
+  // the exact conversion of its bytes, and with four phases for B unit 0 because
   // the last phase of a step still multiplies by rb[0] while the next step's
   // unit is read.
-  bf16x8_t ra[RF][2], rb[2][2][2];
-  uint4 rn[FP8 && FAM != 0 ? 2 : 1][2][FP8 ? 1 : 2];
-  f32x4_t acc[NU][2][RF][2];
+  bf16x8_t ra[RF][2], rb[NB][2][2];
+  uint4 rn[FP8 && !kFour ? NB : 1][2][FP8 ? 1 : 2];
+  f32x4_t acc[NU][NB][RF][2];
   const int wrow = wm * (F::kUnitRows / 2) + rr;
   auto read_a = [&](int u, int stage) {
     const unsigned char* q = smem + stage * F::kStage + u * F::kA + wrow * 128;
@@ -347,7 +361,7 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
     for (int j = 0; j < 2; ++j) {
       const int lr = wn * 32 + j * 16 + rr;
       if constexpr (FP8) {
-        rn[FAM == 0 ? 0 : b][j][0] = *reinterpret_cast<const uint4*>(q + lr * 64 + ((hh ^ ((rr >> 2) & 3)) << 4));
+        rn[kFour ? 0 : b][j][0] = *reinterpret_cast<const uint4*>(q + lr * 64 + ((hh ^ ((rr >> 2) & 3)) << 4));
       } else {
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
@@ -364,12 +378,12 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       if constexpr (FP8) {
-        const uint4 v = rn[FAM == 0 ? 0 : b][j][0];
+        const uint4 v = rn[kFour ? 0 : b][j][0];
         const uint2 w0 = e4m3x4_to_bf16x4(v.x), w1 = e4m3x4_to_bf16x4(v.y);
         const uint2 w2 = e4m3x4_to_bf16x4(v.z), w3 = e4m3x4_to_bf16x4(v.w);
         rb[b][j][0] = __builtin_bit_cast(bf16x8_t, make_uint4(w0.x, w0.y, w1.x, w1.y));
         rb[b][j][1] = __builtin_bit_cast(bf16x8_t, make_uint4(w2.x, w2.y, w3.x, w3.y));
-      } else if (FAM == 0 && b == 0) {
+      } else if (kFour && b == 0) {
 #pragma unroll
         for (int k = 0; k < 2; ++k) rb[0][j][k] = __builtin_bit_cast(bf16x8_t, rn[0][j][k]);
       }
@@ -385,31 +399,30 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
           acc[u][b][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rb[b][j][k], ra[i][k], acc[u][b][i][j], 0, 0, 0);
   };
 
-  Item cur = decode_item<GATED>(p, sc, item, FAM, ncol, KT), nxt = cur;
+  Item cur = decode_item<GATED, FAM, NB>(p, sc, item, ncol, KT), nxt = cur;
   bool split = cur.kn < KT;  // a piece of a tile
   bool has_next = false;     // the stream has moved on to nxt, item nitem
   int nitem = -1;
-  stream_set<GATED, FP8, FAM>(st, p, cur, wave);
+  stream_set<GATED, FP8, FAM, NB>(st, p, cur, wave);
 
   __syncthreads();
   int stage = 0;  // stage of the K step being computed
-  // Loads in flight after the wait of a phase.  Family 0: those of the last
-  // 4 * NST - 2 of its four phases per step; else NST - 2 steps.
-  constexpr int kFlight =
-      FAM == 0 ? (2 * NST - 1) * (F::kLA + F::kLB) : (NST - 2) * (F::kLA + 2 * F::kLB);
+  // Loads in flight after the wait of a phase.  Four phases per step: those of
+  // the last 4 * NST - 2 phases; else NST - 2 steps.
+  constexpr int kFlight = kFour ? (2 * NST - 1) * (F::kLA + F::kLB) : (NST - 2) * (F::kLA + NB * F::kLB);
   static_assert(kFlight < 64, "vmcnt range");
-  constexpr int kAhead = FAM == 0 ? NST : NST - 1;  // steps the stream is ahead
+  constexpr int kAhead = kFour ? NST : NST - 1;  // steps the stream is ahead
   for (int s = 0; s < kAhead; ++s) {
     if (st.left == 0) stream_null(st);
     load_b(0, s);
     load_a(0, s);
-    load_b(1, s);
+    if constexpr (NB == 2) load_b(1, s);
     if constexpr (NU == 2) load_a(1, s);
     st.next();
   }
   wait_vmcnt<kFlight>();
   slot_barrier();
-  if constexpr (FAM == 0) {
+  if constexpr (kFour) {
     read_b(2, 0);
     // the first phase refills this unit, each wave for another one's reads too
     wait_lgkm0();
@@ -421,7 +434,7 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
 #pragma unroll
   for (int u = 0; u < NU; ++u)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int i = 0; i < RF; ++i)
 #pragma unroll
@@ -429,15 +442,15 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
 
   for (;;) {
     if (st.left == 0) {
-      // The stream follows the chain into the next item of the family if this
+      // The stream follows the chain into the next item of the kind if this
       // one is whole and long enough that the stream is at most one item
       // ahead.
       const int ni = !has_next && !split && KT > 2 * NST ? nth_item(sc, r + 1, nwg, xcd, xj) : -1;
-      if (ni >= 0 && item_family(sc, ni) == FAM) {
-        nxt = decode_item<GATED>(p, sc, ni, FAM, ncol, KT);
+      if (ni >= 0 && item_kind(sc, ni) == (FAM | (NB == 1 ? 4 : 0))) {
+        nxt = decode_item<GATED, FAM, NB>(p, sc, ni, ncol, KT);
         nitem = ni;
         has_next = true;
-        stream_set<GATED, FP8, FAM>(st, p, nxt, wave);
+        stream_set<GATED, FP8, FAM, NB>(st, p, nxt, wave);
       } else {
         stream_null(st);
       }
@@ -447,7 +460,7 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
     t -= seg;
     do {
       const int ns = stage + 1 == NST ? 0 : stage + 1;
-      if constexpr (FAM == 0) {
+      if constexpr (kFour) {
         // Four phases per K step, one per (A unit, B unit) pair, in an order
         // in which each needs one new operand unit: A0, B1, A1, then B0 of
         // the next step.  A phase's loads refill the unit that was read one
@@ -472,29 +485,29 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
         // One phase per K step; the stage read in the last phase is refilled.
         const int fs = stage == 0 ? NST - 1 : stage - 1;
         read_a(0, stage);
-        read_b(0, stage);
-        read_b(1, stage);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) read_b(b, stage);
         load_a(0, fs);
-        load_b(0, fs);
-        load_b(1, fs);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) load_b(b, fs);
         st.next();
         wait_vmcnt<kFlight>();
         wait_lgkm0();
-        widen(0);
-        widen(1);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) widen(b);
         slot_barrier();
-        mma(0, 0);
-        mma(0, 1);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) mma(0, b);
         slot_barrier();
       }
       stage = ns;
     } while (--seg);
     if (t > 0) continue;
 
-    constexpr int kPart = F::kRows * kBN;  // floats
-    constexpr int kFrags = NU * 2 * RF * 2;
+    constexpr int kPart = F::kRows * F::kCols;  // floats
+    constexpr int kFrags = NU * NB * RF * 2;
     // split tiles: what the finisher adds to its own sums
-    Piece pc{1, 0, 0, 0, 0};
+    Piece pc{1, 0, 0, 0, 0, 0};
     unsigned tags = 0;
     if (split) {
       pc = decode_piece(sc, item, FAM);
@@ -525,13 +538,13 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
 #pragma unroll
         for (int u = 0; u < NU; ++u)
 #pragma unroll
-          for (int b = 0; b < 2; ++b)
+          for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int i = 0; i < RF; ++i)
 #pragma unroll
               for (int j = 0; j < 2; ++j)
                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[u][b][i][j]), rs, vo,
-                                                       (((u * 2 + b) * RF + i) * 2 + j) * 1024, 16 /* sc1 */);
+                                                       (((u * NB + b) * RF + i) * 2 + j) * 1024, 16 /* sc1 */);
         wait_vmcnt<0>();
         __syncthreads();  // every wave's part has completed
         if (tid == 0)
@@ -576,7 +589,7 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
         for (int i = 0; i < RF; ++i)
 #pragma unroll
           for (int j = 0; j < 2; ++j)
-            v[i][j] = __builtin_amdgcn_raw_buffer_load_b128(rs, vo, (((u * 2 + b) * RF + i) * 2 + j) * 1024,
+            v[i][j] = __builtin_amdgcn_raw_buffer_load_b128(rs, vo, (((u * NB + b) * RF + i) * 2 + j) * 1024,
                                                             16 /* sc1 */);
 #pragma unroll
         for (int i = 0; i < RF; ++i)
@@ -618,16 +631,16 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
                        __uint_as_float(v.y & 0xffff0000u)};
       };
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
+      for (int b = 0; b < NB; ++b) {
         f32x4_t sg, su;
         if constexpr (FP8) {
           if constexpr (GATED) {
-            const int c = cur.nti * (kBN / 2) + wn * 32 + b * 16 + hh * 4;
+            const int c = cur.nti * kOut + wn * (16 * NB) + b * 16 + hh * 4;
             sg = scales(wd->s_gu, c);
             // the up scales start at element n_out, a multiple of 64
             su = scales(wd->s_gu + n_out, c);
           } else {
-            const int c = cur.nti * kBN + b * 128 + wn * 32 + hh * 4;
+            const int c = cur.nti * kOut + b * 128 + wn * 32 + hh * 4;
             sg = scales(wd->s_down, c);
             su = scales(wd->s_down, c + 16);
           }
@@ -645,7 +658,7 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
               for (int j = 0; j < 2; ++j) o[i][j] = acc[u][b][i][j];
           }
           if constexpr (GATED) {
-            const int col = cur.nti * (kBN / 2) + wn * 32 + b * 16 + (hh >> 1) * 8;
+            const int col = cur.nti * kOut + wn * (16 * NB) + b * 16 + (hh >> 1) * 8;
 #pragma unroll
             for (int i = 0; i < RF; i += 2) {
               uint2 w[2];
@@ -666,7 +679,7 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
               store8(w[0], w[1], row0 + (i + (hh & 1)) * 16, col);
             }
           } else {
-            const int col = cur.nti * kBN + b * 128 + wn * 32 + (hh & 1) * 16 + (hh >> 1) * 8;
+            const int col = cur.nti * kOut + b * 128 + wn * 32 + (hh & 1) * 16 + (hh >> 1) * 8;
 #pragma unroll
             for (int i = 0; i < RF; ++i) {
               uint2 w[2];
@@ -700,7 +713,7 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
 #pragma unroll
     for (int u = 0; u < NU; ++u)
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
+      for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int i = 0; i < RF; ++i)
 #pragma unroll
@@ -728,13 +741,19 @@ __global__ __launch_bounds__(512, 2) void ffn_mfma_kernel(const FfnParams p) {
   int r = 0;
   int item = nth_item(sc, r, nwg, xcd, xj);
   while (item >= 0) {
-    const int f = item_family(sc, item);
-    if (f == 0)
-      run_family<GATED, FP8, 0>(p, sc, smem, lds_base, nwg, xcd, xj, r, item);
-    else if (f == 1)
-      run_family<GATED, FP8, 1>(p, sc, smem, lds_base, nwg, xcd, xj, r, item);
+    const int kind = item_kind(sc, item);
+    if (kind == 0)
+      run_family<GATED, FP8, 0, 2>(p, sc, smem, lds_base, nwg, xcd, xj, r, item);
+    else if (kind == 1)
+      run_family<GATED, FP8, 1, 2>(p, sc, smem, lds_base, nwg, xcd, xj, r, item);
+    else if (kind == 2)
+      run_family<GATED, FP8, 2, 2>(p, sc, smem, lds_base, nwg, xcd, xj, r, item);
+    else if (kind == 4)
+      run_family<GATED, FP8, 0, 1>(p, sc, smem, lds_base, nwg, xcd, xj, r, item);
+    else if (kind == 5)
+      run_family<GATED, FP8, 1, 1>(p, sc, smem, lds_base, nwg, xcd, xj, r, item);
     else
-      run_family<GATED, FP8, 2>(p, sc, smem, lds_base, nwg, xcd, xj, r, item);
+      run_family<GATED, FP8, 2, 1>(p, sc, smem, lds_base, nwg, xcd, xj, r, item);
   }
   if (probe) {
     const unsigned long long clk1 = __builtin_amdgcn_s_memtime(), rt1 = __builtin_amdgcn_s_memrealtime();

@@ -173,7 +173,7 @@ __device__ __forceinline__ void copy_pass(gsrc_t src, v4u* dst, int c0, int nchu
 // in front of the gather's own: one thread per cut, the smallest word wins.
 // Beside the copies it costs the drain nothing; every FFN workgroup
 // working it out for itself took 1.0 us of each launch.
-constexpr int kCutBlocks = 4;
+constexpr int kCutBlocks = 8;
 static_assert(kCutBlocks * 256 == 2 * kCuts, "a thread per stage and cut");
 __device__ __forceinline__ void choose_cut(const CutArgs& a, int block) {
   const int stage = block & 1, cut = (block >> 1) * 256 + (int)threadIdx.x;
@@ -181,7 +181,7 @@ __device__ __forceinline__ void choose_cut(const CutArgs& a, int block) {
   sched_tiles(s, uni(a.tile_totals[3 * stage]), uni(a.tile_totals[3 * stage + 1]), uni(a.tile_totals[3 * stage + 2]),
               a.nwg);
   const int KT = stage == 0 ? a.kt[0] : a.kt[1];
-  if (!cut_pays(s, a.nwg, KT)) return;
+  if (!cut_pays(s, a.nwg)) return;
   uint32_t word = cut_word(s, a.fp8, a.nwg, KT, a.split_bytes, cut);
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) word = min(word, (uint32_t)__shfl_xor((int)word, off));

@@ -152,12 +152,13 @@ static bool ordered(const Access& r, const Access& w) {
 }
 
 // The tiles of families 0, 1, 2 in rounds of 8 workgroups: whole[f] rounds of
-// whole tiles, then (tail) 4 tiles of every family in two pieces each.  arrival:
-// this workgroup's place among a tile's pieces.  Returns the number of
+// whole tiles, then (tail) 4 tiles of every family, in column halves (bit 1 of
+// tail), and each of these in two pieces (bit 0).  arrival: this workgroup's
+// place among a tile's pieces.  Returns the number of
 // unordered pairs, the first of them in `msg`; -1 where waves pass different
 // numbers of barriers.
 template <bool GATED, bool FP8>
-static long order_violations(int KT, const int* whole, bool tail, int arrival, int xcd, bool mixed, long* n_reads,
+static long order_violations(int KT, const int* whole, int tail, int arrival, int xcd, bool mixed, long* n_reads,
                              char* msg, int msg_n) {
   static std::vector<unsigned char> mem(kFfnLds);
   lds_mem = mem.data();
@@ -178,7 +179,7 @@ static long order_violations(int KT, const int* whole, bool tail, int arrival, i
   for (int f = 0; f < 3; ++f) all += tiles[f];
   sched_tiles(sc, tiles[0], tiles[1], tiles[2], nwg);
   sc.whole = nwhole;  // (a tail of more than a round stays one)
-  sched_cut(sc, tail ? 1 << 6 | 1 << 3 | 1 : kNoCut, nwg);
+  sched_cut(sc, (tail & 1 ? 1 << 6 | 1 << 3 | 1 : 0) | (tail & 2 ? 1 << 9 : 0), nwg);
   sc.mixed = mixed;
 
   // one group per 4 tiles: 4 columns of tiles, one row tile
@@ -219,13 +220,19 @@ static long order_violations(int KT, const int* whole, bool tail, int arrival, i
     int r = 0;
     int item = nth_item(sc, r, nwg, xcd, 0);
     while (item >= 0) {
-      const int f = item_family(sc, item);
-      if (f == 0)
-        run_family<GATED, FP8, 0>(p, sc, lds_mem, 0, nwg, xcd, 0, r, item);
-      else if (f == 1)
-        run_family<GATED, FP8, 1>(p, sc, lds_mem, 0, nwg, xcd, 0, r, item);
+      const int kind = item_kind(sc, item);
+      if (kind == 0)
+        run_family<GATED, FP8, 0, 2>(p, sc, lds_mem, 0, nwg, xcd, 0, r, item);
+      else if (kind == 1)
+        run_family<GATED, FP8, 1, 2>(p, sc, lds_mem, 0, nwg, xcd, 0, r, item);
+      else if (kind == 2)
+        run_family<GATED, FP8, 2, 2>(p, sc, lds_mem, 0, nwg, xcd, 0, r, item);
+      else if (kind == 4)
+        run_family<GATED, FP8, 0, 1>(p, sc, lds_mem, 0, nwg, xcd, 0, r, item);
+      else if (kind == 5)
+        run_family<GATED, FP8, 1, 1>(p, sc, lds_mem, 0, nwg, xcd, 0, r, item);
       else
-        run_family<GATED, FP8, 2>(p, sc, lds_mem, 0, nwg, xcd, 0, r, item);
+        run_family<GATED, FP8, 2, 1>(p, sc, lds_mem, 0, nwg, xcd, 0, r, item);
     }
     if (barriers >= 0 && epoch != barriers) uneven = true;
     barriers = epoch;
@@ -249,46 +256,50 @@ static long order_violations(int KT, const int* whole, bool tail, int arrival, i
   return bad;
 }
 
-// The cut of a launch of these tiles (pieces per family in bits 4f ..), chosen
-// as the device does.
+// The cut of a launch of these tiles (pieces per family in bits 4f .., column
+// halves in bit 12), chosen as the device does.
 extern "C" int ffn_cut(int fp8, int t0, int t1, int t2, int nwg, int KT, long split_bytes) {
   Sched s;
   sched_tiles(s, t0, t1, t2, nwg);
   uint32_t word = kNoCut;
-  if (cut_pays(s, nwg, KT))
+  if (cut_pays(s, nwg))
     for (int cut = 0; cut < kCuts; ++cut) word = min(word, cut_word(s, fp8, nwg, KT, split_bytes, cut));
   sched_cut(s, word, nwg);
-  return s.nsp;
+  return s.nsp | (s.halves - 1) << 12;
 }
 
 // The largest cost of a workgroup in the last rounds under a cut (pieces per
-// family in bits 4f ..): every workgroup, item by item.  -1: a cut that is
+// family in bits 4f .., halves in bit 12): every workgroup, item by item.  -1: a cut that is
 // not possible.
 extern "C" long ffn_cut_cost(int fp8, int t0, int t1, int t2, int nwg, int KT, long split_bytes, int nsp) {
   Sched s;
   sched_tiles(s, t0, t1, t2, nwg);
+  const int halves = 1 + (nsp >> 12);
   long floats = 0, pieces = 0;
   for (int f = 0; f < 3; ++f) {
     const int n = (nsp >> (4 * f)) & 15;
     if (n > 1 && (s.tail(f) == 0 || KT / n < kMinSplitSteps)) return -1;
     floats += (long)s.tail(f) * (n - 1) * (kBM >> f) * kBN;
-    pieces += (long)s.tail(f) * n;
+    pieces += (long)s.tail(f) * halves * n;
   }
   if (4 * floats > split_bytes || pieces > 4 * nwg) return -1;
-  s.nsp = nsp;
-  for (int f = 0; f < 3; ++f) s.items += s.tail(f) * (s.pieces(f) - 1);
+  s.nsp = nsp & 0xfff;
+  s.halves = halves;
+  for (int f = 0; f < 3; ++f) s.items += s.tail(f) * (s.pieces(f) * halves - 1);
   const int base0 = max(0, s.whole - nwg);
   std::vector<long> sum(nwg, 0);
   for (int item = base0; item < s.items; ++item) {
     const int f = item_family(s, item), r = (item - base0) / nwg, at = (item - base0) % nwg;
-    sum[r & 1 ? nwg - 1 - at : at] += item < s.whole ? step_cost(fp8, f) * KT : piece_cost(fp8, f, KT, s.pieces(f));
+    const int busy = min(nwg, s.items - item / nwg * nwg);
+    sum[r & 1 ? nwg - 1 - at : at] += item < s.whole ? piece_time(fp8, f, 1, KT, 1, nwg, nwg)
+                                                     : piece_time(fp8, f, halves, KT, s.pieces(f), busy, nwg);
   }
   return *std::max_element(sum.begin(), sum.end());
 }
 
 extern "C" long ffn_order_violations(int gated, int fp8, int KT, const int* whole, int tail, int arrival, int xcd,
                                      int mixed, long* n_reads, char* msg, int msg_n) {
-  auto go = [&](auto fn) { return fn(KT, whole, tail != 0, arrival, xcd, mixed != 0, n_reads, msg, msg_n); };
+  auto go = [&](auto fn) { return fn(KT, whole, tail, arrival, xcd, mixed != 0, n_reads, msg, msg_n); };
   if (gated) return fp8 ? go(order_violations<true, true>) : go(order_violations<true, false>);
   return fp8 ? go(order_violations<false, true>) : go(order_violations<false, false>);
 }

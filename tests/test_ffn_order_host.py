@@ -21,8 +21,8 @@ def lib():
     return so
 
 
-# whole rounds per family, tail in two pieces, this workgroup's arrival, XCD,
-# two directions
+# whole rounds per family, tail (1: two pieces, 2: column halves, 3: both), this
+# workgroup's arrival, XCD, two directions
 CHAINS = {
     "family0": ((3, 0, 0), 0, 0, 0, 0),
     "family1": ((0, 3, 0), 0, 0, 0, 0),
@@ -32,6 +32,11 @@ CHAINS = {
     "pieces_first": ((1, 0, 0), 1, 0, 0, 0),
     "pieces_last": ((1, 0, 0), 1, 1, 0, 0),
     "pieces_reversed": ((1, 1, 1), 1, 1, 1, 1),
+    "halves": ((0, 0, 0), 2, 0, 0, 0),
+    "halves_last": ((1, 0, 0), 2, 0, 0, 0),
+    "halves_reversed": ((1, 1, 1), 2, 0, 1, 1),
+    "halves_pieces_first": ((1, 0, 0), 3, 0, 0, 0),
+    "halves_pieces_last": ((0, 0, 0), 3, 1, 0, 0),
 }
 
 
@@ -42,7 +47,7 @@ def test_lds_reads_and_refills_are_ordered(lib, chain, gated, fp8):
     whole, tail, arrival, xcd, mixed = CHAINS[chain]
     # fewer, as many and more K steps than a ring has stages, odd and even;
     # pieces need at least 8 steps each
-    for kt in (16, 17, 23) if tail else (1, 2, 3, 4, 5, 13, 14):
+    for kt in (16, 17, 23) if tail & 1 else (1, 2, 3, 4, 5, 13, 14):
         n, msg = ctypes.c_long(0), ctypes.create_string_buffer(256)
         bad = lib.ffn_order_violations(gated, fp8, kt, (ctypes.c_int * 3)(*whole), tail, arrival, xcd, mixed,
                                        ctypes.byref(n), msg, 256)

@@ -3,7 +3,9 @@ oracle element by element: remainders on both sides of 64, 128 and 256 rows,
 column counts that end inside a 256-column tile, K of fewer, as many and more
 steps than a ring has stages, launches of several rounds whose workgroups
 chain tiles of one family and then change to the next, and tails whose tiles
-are cut along K (reruns bit-identical)."""
+are cut into column halves and along K (reruns bit-identical).  How the tails
+are cut is a choice of the cost model; test_ffn_cut_host.py holds CUTS to it on
+256 CUs."""
 
 import numpy as np
 import pytest
@@ -26,8 +28,29 @@ CASES = {
     # 9 rounds of gate/up tiles of all three families (f / 128 = 72 column
     # tiles), 24 and 144 steps in the two launches
     "rounds": ([1100, 700, 300, 200, 100, 90, 50, 20] * 2, 1536, 9216),
-    # a tail of all three families over few CUs, up to 8 pieces
+    # a tail of all three families over few CUs: gate/up 8 steps, down 64
     "tail": ([300, 100, 30], 512, 4096),
+    # column halves, last ones that hold 64 columns, and none: 4.5 tiles of 128
+    # features, 2.25 of 256 columns
+    "halves": ([60, 340], 576, 576),
+    # halves in pieces, in the down and in the gate/up launch
+    "halves_pieces_down": ([300, 128], 576, 4160),
+    "halves_pieces_gate_up": ([300, 128], 4160, 576),
+    # whole tiles in pieces: all families at once, and 128-row tiles alone
+    "whole_pieces": (([200, 100, 40] * 11)[:32], 320, 5120),
+    "whole_pieces_128": ([100] * 34, 320, 5120),
+    # more pieces would need more than the partial sums' area
+    "area": ([520] * 19, 64, 6144),
+}
+# per launch (gate/up, down): column halves or not, and the families whose
+# tiles or halves are cut into pieces
+CUTS = {
+    "halves": ((2, ()), (2, ())),
+    "halves_pieces_down": ((2, ()), (2, (0, 1, 2))),
+    "halves_pieces_gate_up": ((2, (0, 1, 2)), (2, ())),
+    "whole_pieces": (None, (1, (0, 1, 2))),
+    "whole_pieces_128": (None, (1, (1,))),
+    "tail": ((2, ()), (2, (0, 1, 2))),
 }
 
 
