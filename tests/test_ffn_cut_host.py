@@ -12,6 +12,7 @@ import pytest
 
 import ffn_host
 import test_gpu_ffn_edges
+import test_gpu_tile_families
 
 SPLIT_BYTES = 128 * 256 * 256 * 4
 NWG = 256
@@ -114,6 +115,7 @@ def _launches(depths, d, f):
 
 
 GPU_CASES = [(test_gpu_ffn_edges.CASES[n], c) for n, c in test_gpu_ffn_edges.CUTS.items()]
+GPU_CASES += [(test_gpu_tile_families.SPLIT_CASES[n], c) for n, c in test_gpu_tile_families.CUTS.items()]
 
 
 @pytest.mark.parametrize("fp8", [0, 1])

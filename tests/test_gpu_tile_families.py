@@ -1,16 +1,12 @@
 """GPU parity of every row-tile choice the plan makes, on explicit per-expert
 queue depths (rows mode), against the oracle element by element.
 
-Cold batch (its full 256-row tiles do not fill one round of the grid): a
-remainder above 128 rows takes one tall 256-row tile, 65..128 rows one medium
-tile, 1..64 rows one small tile.  Warm batch, per FFN stage: a remainder
-above 128 rows takes one more big tile (rule B), unless those extra big
-tiles would start another round of the grid in a stage with fewer than 4
-rounds; then only a remainder above 192 rows does (rule A) and the others
-take medium tiles and at most one small tile.  The depths below put at least
-one expert on each branch (and exact multiples of 256, and empty experts),
-for bf16 and fp8 weights; the mixed batch splits the same remainder
-differently in its two stages."""
+An expert's rows are covered by full 256-row tiles and one remainder tile of
+the smallest height (256, 128 or 64 rows) that holds the rest.  The depths below
+put at least one expert on each choice, with exact multiples of 256 and empty
+experts among them, for bf16 and fp8 weights, in launches of less than a round
+of tiles and of several; the last rounds are cut into column halves and along K
+(test_ffn_cut_host.py holds the cuts that CUTS names on 256 CUs)."""
 
 import dataclasses
 
@@ -24,14 +20,13 @@ from gpu_helpers import BF16_RTOL, assert_close, log, make_context, to_dev, to_h
 
 pytestmark = pytest.mark.gpu
 
-COLD = [300, 200, 100, 40, 1, 256, 0, 129]          # big+small, tall, medium, small, small, big, -, tall
-# rule B in both stages: 8 big + small, big, big, big + small, big + small, -,
-# 2 big, big, medium
+# heights of the remainder tiles: 64, 256, 128, 64, 64, none, -, 256
+COLD = [300, 200, 100, 40, 1, 256, 0, 129]
+# f = 8192 (64 gate/up column tiles): more than four rounds of gate/up tiles,
+# remainders of all heights; down is one partial round of 19 tiles
 WARM = [2100, 230, 150, 300, 260, 0, 512, 193, 100]
-# d = 512, f = 896: 128 big row tiles under rule A, 129 under rule B.  Gate/up
-# (7 big column tiles) has 4 rounds either way: rule B, so the 150-row
-# remainder takes a big tile.  Down (2 big column tiles) would go from 1 round
-# to 2: rule A, so that remainder takes a medium and a small tile.
+# 13 experts without a remainder and one of each height: gate/up (7 column
+# tiles) of 256-row tiles for three and a half rounds, down (2) of one and a tail
 MIXED = [2048] * 13 + [2198, 2148, 2088]
 
 
@@ -53,11 +48,9 @@ def _rows(w, depths, seed):
                                       ("short2", "bf16"), ("short2", "fp8")])
 def test_tile_families_match_oracle(kind, wdt):
     # short1 / short2: the cold depths with K of 1, 2 or 3 steps of 64 in the
-    # two stages, fewer than every ring's stages (the first pass of a refill
-    # repeats loads of the prologue; past the last step loads repeat it)
+    # two stages, no more than the rings' stages (loads past the last step are
+    # out of range)
     depths = {"cold": COLD, "warm": WARM, "mixed": MIXED, "short1": COLD, "short2": COLD}[kind]
-    # warm: f = 8192 gives 64 big gate/up column tiles, so 8 + 2 + 1 + 1 + 1
-    # full 256-row blocks fill more than one round of 256 CUs
     d, f = {"cold": (256, 320), "warm": (256, 8192), "mixed": (512, 896), "short1": (64, 192),
             "short2": (128, 64)}[kind]
     w = synth.Workload(f"fam_{kind}_{wdt}", 110, d=d, f=f, E=len(depths), k=1, zipf_s=1.0, mode="rows",
@@ -87,25 +80,29 @@ def test_tile_families_match_oracle(kind, wdt):
     del ctx, dev_w, keep
 
 
-# Split-K: a launch of at most half a grid of tiles cuts every tile into
-# n_split = min(4, grid / tiles, K / 512) pieces of consecutive K steps (the
-# slot area permitting); the last piece to finish adds the pieces' f32
-# partial sums in piece order.  Each case below puts at most 128 tiles into
-# at least one launch with K >= 1024, on the families named.
+# Launches of less than a round of tiles, which are cut to fill the grid.
 SPLIT_CASES = {
-    # 2 experts x 16 rows, small tiles: gate/up 32 tiles in 4 pieces, down 32 in 2
+    # 2 experts of 16 rows: 16 gate/up tiles in halves of 3 pieces (32 K steps),
+    # 16 down tiles (16 steps) in halves
     "small": ([16, 16], 2048, 1024),
-    # medium (100 rows) and tall (200 rows) tiles of a cold batch, 4 pieces
+    # a 128-row and a 256-row tile per column: only the latter's halves in pieces
     "medium_tall": ([100, 200], 2048, 1024),
-    # one 256-row expert: 16 big gate/up tiles in 2 pieces, 4 big down tiles in 4
+    # one 256-row expert: 16 gate/up tiles in halves, 4 down tiles in halves of
+    # 3 pieces
     "big": ([256], 1024, 2048),
-    # every family in one launch (big + medium, small, tall; an empty expert):
-    # 56 gate/up and 28 down tiles, 2 pieces each
+    # every family in both launches and an empty expert, 16 K steps: halves
     "mixed": ([356, 30, 0, 200], 1024, 1024),
-    # 100 big gate/up tiles (f = 12800): 2 pieces would need 50 MB of partial
-    # sums, more than the 32 MB area, so that launch is not split; the down
-    # launch (4 big tiles, K = 12800) is, in 4 pieces
+    # 100 gate/up tiles in halves, which need none of the partial sums' area; 4
+    # down tiles, whose 200 K steps are cut furthest: halves of 7 or 8 pieces
     "area_cap": ([256], 1024, 12800),
+}
+# as in test_gpu_ffn_edges.py
+CUTS = {
+    "small": ((2, (2,)), None),
+    "medium_tall": ((2, (0,)), None),
+    "big": (None, (2, (0,))),
+    "mixed": ((2, ()), (2, ())),
+    "area_cap": (None, (2, (0,))),
 }
 
 
@@ -149,11 +146,10 @@ def test_split_k_matches_oracle(kind, wdt):
 
 # Expert shapes of the weight-streaming sweep at their real sizes (the bench
 # runs more experts of each): same-shape experts of n rows each.  Mixtral
-# shape, 4 x 16 rows: 448 small gate/up tiles, and a down launch of 128 small
-# tiles (K = 14336) split in 2; EP-share shape with fp8 weights, 12 x 64
-# rows: 192 wide (64 x 256) small tiles per launch, not split; and, smaller
-# than any sweep shape so that its fp8 weights quantise in seconds, a long-K
-# fp8 down launch of 16 wide tiles (K = 4096) split in 4.
+# shape, 4 x 16 rows: 448 gate/up tiles, one round and a tail of 192, and a down
+# launch of 64 tiles of 224 K steps; EP-share shape with fp8 weights, 12 x 64
+# rows: 192 tiles per launch; and, smaller than any sweep shape so that its fp8
+# weights quantise in seconds, a long-K fp8 down launch of 16 tiles.
 SWEEP_CASES = {
     "d4096_f14336_bf16_n16": (4, 16, 4096, 14336, "bf16"),
     "d4096_f2048_fp8_n64": (12, 64, 4096, 2048, "fp8"),
