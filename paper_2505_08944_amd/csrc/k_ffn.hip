@@ -65,9 +65,7 @@ typedef __attribute__((address_space(3))) void* lds_vptr;
 // A raw buffer resource over [base, base + bytes): stride 0, 32-bit data
 // format, every access bounds-checked against bytes (an access past the end
 // reads zeros without touching memory and writes nothing).  Its words are
-// kept apart, as scalars, and only put together where a load uses them: as
-// one four-word value that is changed word by word (null below) across the
-// branches of a chain, the compiler let a branch keep stale words.
+// kept apart, as scalars, and only put together where a load uses them.
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 struct Rsrc {
   int lo, hi, bytes;
@@ -95,7 +93,11 @@ __device__ __forceinline__ const_ptr<T> as_const(const T* p) {
 // lds_addr).  Issued through inline asm so that the compiler does not see an
 // LDS write it cannot disambiguate (it would otherwise wait for every
 // outstanding load before each LDS read); the kernel orders these loads
-// itself with wait_vmcnt + barriers.
+// itself with wait_vmcnt + barriers.  Nor does the compiler see to the wait
+// states that such a load needs: one after the write of M0 (here), five after
+// a vector instruction writes one of its scalar registers.  Waiting for these
+// here as well (s_nop 3) cost 2 - 3% of large launches; test_ffn_waits_host.py
+// follows every path into every load of the built code instead.
 __device__ __forceinline__ void dload16(i32x4_t rsrc, uint32_t voff, uint32_t soff, uint32_t lds_addr) {
   // (one wait state between the write of M0 and its use)
   asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(rsrc),
