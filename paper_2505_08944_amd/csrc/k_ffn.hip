@@ -19,13 +19,16 @@
 // operands from LDS and issues the direct-to-LDS loads of a later K step; the
 // next slot swaps the roles.  The matrix cores therefore always have a wave
 // with its operands in registers, and the memory slot's latencies hide behind
-// the other group's MFMAs.  Measured on the hot loop (8192 rows, d = 4096,
-// f = 14336): 2220 / 2144 cycles per K step in gate/up / down against the
-// 2048 its MFMAs take; one wave per SIMD (four waves of 128 x 128, the operand
-// reads and refills spread between the MFMAs) took about 3000.  At that duty
-// the shader clock is what the power limit leaves (1.5 - 1.65 GHz), which is
-// why the MFMA shape matters: 16x16x32 ran the same loop at 1.5 - 1.6 GHz,
-// 32x32x16 (twice the accumulator traffic per operation) at 1.3 - 1.4.
+// the other group's MFMAs.  One expert of 8192 rows (d = 4096, f = 14336, whole
+// rounds of tiles, launches back to back): 2600 / 2500 cycles per K step in
+// gate/up / down, prologues and epilogues included, against the 2048 its MFMAs
+// take, at 1.8 GHz; a card that held 1.5 - 1.65 GHz took 2220 / 2144 cycles,
+// the same 1.4 us, so neither the clock nor the cycles bound it alone.  One wave
+// per SIMD (four waves of 128 x 128, the operand reads and refills spread
+// between the MFMAs) took about 3000 cycles there.  The shader clock under this
+// load is what the power limit leaves, so the MFMA shape matters: 32x32x16
+// (twice the accumulator traffic per operation) ran at 1.3 - 1.4 GHz on the
+// card where 16x16x32 ran at 1.5 - 1.6.
 //
 // f32 path (f32 activations and weights): 64 x 64 tiles of 32 x 32 f32 MFMA
 // blocks, operands straight from global memory.
@@ -625,7 +628,8 @@ __device__ __forceinline__ void run_family(const FfnParams& p, const Sched& sc, 
         return __builtin_bit_cast(uint32_t, v);
       };
       const const_ptr<WeightDesc> wd = as_const(p.wtab) + cur.g;
-      // four bf16 scales from column c on
+      // four bf16 scales from column c on: vector loads, as lanes differ; the
+      // wait for them drains the ring once per tile
       auto scales = [&](const uint16_t* s, int c) {
         uint2 v;  // the caller's scales are 2-byte aligned
         __builtin_memcpy(&v, s + min(c, n_out - 4), 8);

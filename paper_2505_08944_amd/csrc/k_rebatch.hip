@@ -17,7 +17,8 @@
 // whole wave on one row, so each row is one contiguous coalesced stream; up
 // to 8 loads per lane in flight before the stores); lane 0 records the row's
 // token and gate weight and the (token, slot) -> row map.  Shared-expert rows
-// copy every token's row in id order.
+// copy every token's row in id order.  The first few workgroups choose how the
+// last round of each FFN launch is cut.
 #include <algorithm>
 
 #include "ffn_sched.h"
