@@ -106,86 +106,90 @@ __device__ __forceinline__ int cut_halves(int cut) { return 1 + (cut >> (3 * kCu
 // to 28 in 64-row ones.  The cuts that these constants choose for 844 launches
 // of 1 to 32 experts, each timed under all cuts worth trying, were 0.9% slower
 // than the best on average.
-__device__ __forceinline__ int step_time(bool fp8, int f, int halves, int busy, int nwg) {
+__device__ __forceinline__ float step_time(bool fp8, int f, int halves, float busy) {
   const int lo = fp8 ? (halves == 1 ? (f == 0 ? 165 : f == 1 ? 70 : 60) : (f == 0 ? 85 : f == 1 ? 65 : 45))
                      : (halves == 1 ? (f == 0 ? 75 : f == 1 ? 70 : 60) : (f == 0 ? 60 : f == 1 ? 45 : 35));
   const int hi = fp8 ? (halves == 1 ? (f == 0 ? 165 : f == 1 ? 100 : 90) : (f == 0 ? 100 : f == 1 ? 65 : 50))
                      : (halves == 1 ? (f == 0 ? 175 : f == 1 ? 150 : 145) : (f == 0 ? 105 : f == 1 ? 80 : 75));
-  return lo + (hi - lo) * busy / nwg;
+  return (float)lo + (float)(hi - lo) * busy;
 }
-__device__ __forceinline__ int piece_time(bool fp8, int f, int halves, int KT, int n, int busy, int nwg) {
-  const int sums = f == 0 ? 515 + 325 * n : f == 1 ? 420 + 270 * n : 335 + 195 * n;
-  return step_time(fp8, f, halves, busy, nwg) * KT / n + (n == 1 ? 0 : halves == 1 ? sums : sums * 4 / 5);
+__device__ __forceinline__ float sums_time(int f, int halves, int n) {
+  const int t = f == 0 ? 515 + 325 * n : f == 1 ? 420 + 270 * n : 335 + 195 * n;
+  return n == 1 ? 0.f : (halves == 1 ? 1.f : 0.8f) * (float)t;
 }
 // f32 values of one piece's sums
 __device__ __forceinline__ int part_floats(int f, int halves) { return ((kBM * kBN) >> f) / halves; }
 
-// The time of the last rounds under a cut: the largest sum of one workgroup's
-// items, from the round before the tail on (its items may differ in size), in
-// the order in which they are dealt.  A workgroup's sum changes only where one
-// of its rounds passes from one kind of item to the next, so the slots that
-// follow such a passage, and slot 0, stand for all.
-__device__ __forceinline__ int cut_time(const Sched& s, bool fp8, int nwg, int KT, int halves, const int (&n)[3]) {
-  int end[3], items = s.whole;
+// What a cut makes of the last rounds, from the round before the tail on (its
+// items may differ in size): where the kinds of items end, and their times.
+struct CutRounds {
+  int base0, last, items;  // first and last round's first item, items in all
+  int w0, w1, end[3];      // last item + 1: whole tiles of families 0 and 1, pieces of each family
+  float w[3], c[3], cl[3];  // a whole tile; a piece, in a full round and in the last
+  float inv_nwg;
+};
+
+// False: the cut is not possible.
+__device__ __forceinline__ bool cut_rounds(CutRounds& q, const Sched& s, bool fp8, int nwg, int KT, int64_t split_bytes,
+                                           int cut) {
+  const int halves = cut_halves(cut);
+  int64_t floats = 0;
+  q.items = s.whole;
 #pragma unroll
   for (int f = 0; f < 3; ++f) {
-    items += s.tail(f) * halves * n[f];
-    end[f] = items;
+    const int n = cut_pieces(cut, f), tl = s.tail(f) * halves;
+    if (n > 1 && (tl == 0 || KT < n * kMinSplitSteps)) return false;
+    floats += (int64_t)tl * ((n - 1) * part_floats(f, halves));
+    q.items += tl * n;
+    q.end[f] = q.items;
   }
-  const int base0 = max(0, s.whole - nwg), last = (items - 1) / nwg * nwg;
-  int w[3], c[3], cl[3];  // a whole tile; an item of the tail, in a full round and in the last
+  if (floats * 4 > split_bytes || q.items - s.whole > 4 * nwg) return false;
+  q.inv_nwg = __builtin_amdgcn_rcpf((float)nwg);
+  q.base0 = max(0, s.whole - nwg);
+  q.last = (int)(((float)q.items - 0.5f) * q.inv_nwg) * nwg;
+  q.w0 = min(s.b1, s.whole);
+  q.w1 = min(s.b2, s.whole);
+  const float busy = (float)(q.items - q.last) * q.inv_nwg;
 #pragma unroll
   for (int f = 0; f < 3; ++f) {
-    w[f] = piece_time(fp8, f, 1, KT, 1, nwg, nwg);
-    c[f] = piece_time(fp8, f, halves, KT, n[f], nwg, nwg);
-    cl[f] = piece_time(fp8, f, halves, KT, n[f], items - last, nwg);
+    const int n = cut_pieces(cut, f);
+    const float steps = (float)KT * __builtin_amdgcn_rcpf((float)n), sums = sums_time(f, halves, n);
+    q.w[f] = step_time(fp8, f, 1, 1.f) * (float)KT;
+    q.c[f] = step_time(fp8, f, halves, 1.f) * steps + sums;
+    q.cl[f] = step_time(fp8, f, halves, busy) * steps + sums;
   }
-  const int w0 = min(s.b1, s.whole), w1 = min(s.b2, s.whole);
-  auto load = [&](int lin) {
-    int sum = 0, at = lin;
-    for (int base = base0; base < items; base += nwg) {
-      const int it = base + at;
-      at = nwg - 1 - at;  // the next round is reversed
-      if (it < s.whole)
-        sum += it < w0 ? w[0] : it < w1 ? w[1] : w[2];
-      else if (it < end[0])
-        sum += base == last ? cl[0] : c[0];
-      else if (it < end[1])
-        sum += base == last ? cl[1] : c[1];
-      else if (it < end[2])
-        sum += base == last ? cl[2] : c[2];
-    }
-    return sum;
-  };
-  int worst = load(0);
-  const int edge[6] = {w0, w1, s.whole, end[0], end[1], end[2]};
-#pragma unroll
-  for (int i = 0; i < 6; ++i) {
-    const int e = edge[i];
-    if (e <= base0 || (i > 0 && e == edge[i - 1])) continue;
-    const int r = (e - base0) / nwg, at = e - base0 - r * nwg;
-    if (at > 0) worst = max(worst, load(r & 1 ? nwg - at : at));
+  return true;
+}
+
+// A workgroup's sum over these rounds, in the order in which items are dealt,
+// changes only where one of its rounds passes from one kind of item to the
+// next; the workgroups that follow such a passage, and the first, stand for
+// all.  This is the sum of the i-th of them (of kCutSlots); the largest is the
+// time of the cut.
+constexpr int kCutSlots = 8;
+__device__ __forceinline__ float cut_load(const CutRounds& q, const Sched& s, int nwg, int i) {
+  const int e = i == 1 ? q.w0 : i == 2 ? q.w1 : i == 3 ? s.whole : i == 4 ? q.end[0] : i == 5 ? q.end[1]
+              : i == 6 ? q.end[2] : q.base0;
+  const int d = max(0, e - q.base0), r = (int)(((float)d + 0.5f) * q.inv_nwg), p = d - r * nwg;
+  int at = p == 0 ? 0 : (r & 1) ? nwg - p : p;
+  float sum = 0.f;
+  for (int base = q.base0; base < q.items; base += nwg) {
+    const int it = base + at;
+    at = nwg - 1 - at;  // the next round is reversed
+    const bool last = base == q.last;
+    const float t0 = last ? q.cl[0] : q.c[0], t1 = last ? q.cl[1] : q.c[1], t2 = last ? q.cl[2] : q.c[2];
+    const float tw = it < q.w0 ? q.w[0] : it < q.w1 ? q.w[1] : q.w[2];
+    const float tp = it < q.end[0] ? t0 : it < q.end[1] ? t1 : it < q.end[2] ? t2 : 0.f;
+    sum += it < s.whole ? tw : tp;
   }
-  return worst;
+  return sum;
 }
 
 // (time, cut) in one word: the smallest word is the cut to take, the fewest
-// pieces where times are equal.  ~0: not possible.
+// pieces where times are equal.  ~0: no cut.
 constexpr uint32_t kNoCut = 0xffffffffu;
-__device__ __forceinline__ uint32_t cut_word(const Sched& s, bool fp8, int nwg, int KT, int64_t split_bytes,
-                                             int cut) {
-  const int n[3] = {cut_pieces(cut, 0), cut_pieces(cut, 1), cut_pieces(cut, 2)}, halves = cut_halves(cut);
-  int64_t floats = 0;
-  int items = 0;
-#pragma unroll
-  for (int f = 0; f < 3; ++f) {
-    const int tl = s.tail(f) * halves;
-    if (n[f] > 1 && (tl == 0 || KT < n[f] * kMinSplitSteps)) return kNoCut;
-    floats += (int64_t)tl * ((n[f] - 1) * part_floats(f, halves));
-    items += tl * n[f];
-  }
-  if (floats * 4 > split_bytes || items > 4 * nwg) return kNoCut;
-  return (uint32_t)min(cut_time(s, fp8, nwg, KT, halves, n), (1 << (31 - 3 * kCutBits)) - 2) * kCuts + (uint32_t)cut;
+__device__ __forceinline__ uint32_t cut_word(float time, int cut) {
+  return (uint32_t)min(time, (float)((1 << (31 - 3 * kCutBits)) - 2)) * kCuts + (uint32_t)cut;
 }
 // Something to gain: a tail, and no small share of many rounds.  (And a counter
 // for each half of up to nwg - 1 tiles.)

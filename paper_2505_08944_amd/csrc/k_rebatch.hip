@@ -171,22 +171,31 @@ __device__ __forceinline__ void copy_pass(gsrc_t src, v4u* dst, int c0, int nchu
 }
 
 // The cuts of both FFN launches' last rounds, chosen by kCutBlocks workgroups
-// in front of the gather's own: one thread per cut, the smallest word wins.
-// Beside the copies it costs the drain nothing; every FFN workgroup
-// working it out for itself took 1.0 us of each launch.
-constexpr int kCutBlocks = 8;
-static_assert(kCutBlocks * 256 == 2 * kCuts, "a thread per stage and cut");
+// in front of the gather's own: kCutSlots threads per cut, the smallest word
+// wins.  With one thread per cut a gather of few rows waited for them (340 rows
+// of 8 KB: 7.4 us on average, now 6.3); every FFN workgroup working it
+// out for itself took 1.0 us of each launch.
+constexpr int kCutBlocks = 64;
+static_assert(kCutBlocks * 256 == 2 * kCuts * kCutSlots && kCutSlots == 8, "threads per stage, cut and slot");
 __device__ __forceinline__ void choose_cut(const CutArgs& a, int block) {
-  const int stage = block & 1, cut = (block >> 1) * 256 + (int)threadIdx.x;
+  const int stage = block & 1, id = (block >> 1) * 256 + (int)threadIdx.x, cut = id / kCutSlots;
   Sched s;
   sched_tiles(s, uni(a.tile_totals[3 * stage]), uni(a.tile_totals[3 * stage + 1]), uni(a.tile_totals[3 * stage + 2]),
               a.nwg);
-  const int KT = stage == 0 ? a.kt[0] : a.kt[1];
   if (!cut_pays(s, a.nwg)) return;
-  uint32_t word = cut_word(s, a.fp8, a.nwg, KT, a.split_bytes, cut);
+  CutRounds q;
+  const bool ok = cut_rounds(q, s, a.fp8, a.nwg, stage == 0 ? a.kt[0] : a.kt[1], a.split_bytes, cut);
+  float time = ok ? cut_load(q, s, a.nwg, id % kCutSlots) : 0.f;
 #pragma unroll
-  for (int off = 1; off < 64; off <<= 1) word = min(word, (uint32_t)__shfl_xor((int)word, off));
-  if ((threadIdx.x & 63) == 0) atomicMin(reinterpret_cast<uint32_t*>(a.tile_totals) + kCutWord + stage, word);
+  for (int off = 1; off < kCutSlots; off <<= 1) time = fmaxf(time, __shfl_xor(time, off));
+  uint32_t word = ok ? cut_word(time, cut) : kNoCut;
+#pragma unroll
+  for (int off = kCutSlots; off < 64; off <<= 1) word = min(word, (uint32_t)__shfl_xor((int)word, off));
+  __shared__ uint32_t best[4];
+  if ((threadIdx.x & 63) == 0) best[threadIdx.x >> 6] = word;
+  __syncthreads();
+  word = min(min(best[0], best[1]), min(best[2], best[3]));
+  if (threadIdx.x == 0 && word != kNoCut) atomicMin(reinterpret_cast<uint32_t*>(a.tile_totals) + kCutWord + stage, word);
 }
 
 // LANES: E <= 64, an offset per lane.  57344 rows of 4 KB take 71 us, 3.3 TB/s

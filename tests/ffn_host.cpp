@@ -262,8 +262,14 @@ extern "C" int ffn_cut(int fp8, int t0, int t1, int t2, int nwg, int KT, long sp
   Sched s;
   sched_tiles(s, t0, t1, t2, nwg);
   uint32_t word = kNoCut;
+  CutRounds q;
   if (cut_pays(s, nwg))
-    for (int cut = 0; cut < kCuts; ++cut) word = min(word, cut_word(s, fp8, nwg, KT, split_bytes, cut));
+    for (int cut = 0; cut < kCuts; ++cut)
+      if (cut_rounds(q, s, fp8, nwg, KT, split_bytes, cut)) {
+        float time = 0.f;
+        for (int i = 0; i < kCutSlots; ++i) time = max(time, cut_load(q, s, nwg, i));
+        word = min(word, cut_word(time, cut));
+      }
   sched_cut(s, word, nwg);
   return s.nsp | (s.halves - 1) << 12;
 }
@@ -271,7 +277,7 @@ extern "C" int ffn_cut(int fp8, int t0, int t1, int t2, int nwg, int KT, long sp
 // The largest cost of a workgroup in the last rounds under a cut (pieces per
 // family in bits 4f .., halves in bit 12): every workgroup, item by item.  -1: a cut that is
 // not possible.
-extern "C" long ffn_cut_cost(int fp8, int t0, int t1, int t2, int nwg, int KT, long split_bytes, int nsp) {
+extern "C" double ffn_cut_cost(int fp8, int t0, int t1, int t2, int nwg, int KT, long split_bytes, int nsp) {
   Sched s;
   sched_tiles(s, t0, t1, t2, nwg);
   const int halves = 1 + (nsp >> 12);
@@ -287,12 +293,13 @@ extern "C" long ffn_cut_cost(int fp8, int t0, int t1, int t2, int nwg, int KT, l
   s.halves = halves;
   for (int f = 0; f < 3; ++f) s.items += s.tail(f) * (s.pieces(f) * halves - 1);
   const int base0 = max(0, s.whole - nwg);
-  std::vector<long> sum(nwg, 0);
+  std::vector<double> sum(nwg, 0.);
   for (int item = base0; item < s.items; ++item) {
     const int f = item_family(s, item), r = (item - base0) / nwg, at = (item - base0) % nwg;
-    const int busy = min(nwg, s.items - item / nwg * nwg);
-    sum[r & 1 ? nwg - 1 - at : at] += item < s.whole ? piece_time(fp8, f, 1, KT, 1, nwg, nwg)
-                                                     : piece_time(fp8, f, halves, KT, s.pieces(f), busy, nwg);
+    const int busy = min(nwg, s.items - item / nwg * nwg), n = s.pieces(f);
+    sum[r & 1 ? nwg - 1 - at : at] +=
+        item < s.whole ? (double)step_time(fp8, f, 1, 1.f) * KT
+                       : (double)step_time(fp8, f, halves, (float)busy / (float)nwg) * KT / n + sums_time(f, halves, n);
   }
   return *std::max_element(sum.begin(), sum.end());
 }

@@ -23,7 +23,7 @@ def lib():
     so = ffn_host.load()
     so.ffn_cut.argtypes = [ctypes.c_int] * 6 + [ctypes.c_long]
     so.ffn_cut_cost.argtypes = [ctypes.c_int] * 6 + [ctypes.c_long, ctypes.c_int]
-    so.ffn_cut_cost.restype = ctypes.c_long
+    so.ffn_cut_cost.restype = ctypes.c_double
     return so
 
 
@@ -37,7 +37,8 @@ def _check(lib, fp8, tiles, kt, nwg=NWG, split_bytes=SPLIT_BYTES):
         assert got == 0x111, (tiles, kt)
         return
     assert got in possible, (tiles, kt, hex(got))
-    assert possible[got] == min(possible.values()), (tiles, kt, hex(got))
+    # times are compared in whole units of f32 sums
+    assert possible[got] <= min(possible.values()) * (1 + 1e-5) + 1, (tiles, kt, hex(got))
 
 
 @pytest.mark.parametrize("fp8", [0, 1])
