@@ -172,9 +172,10 @@ __device__ __forceinline__ void copy_pass(gsrc_t src, v4u* dst, int c0, int nchu
 
 // The cuts of both FFN launches' last rounds, chosen by kCutBlocks workgroups
 // in front of the gather's own: kCutSlots threads per cut, the smallest word
-// wins.  With one thread per cut a gather of few rows waited for them (340 rows
-// of 8 KB: 7.4 us on average, now 6.3); every FFN workgroup working it
-// out for itself took 1.0 us of each launch.
+// wins.  A gather of few rows still waits for them a little: single-expert
+// drains of a 1024-token layer, 4.9 us on average without, 6.3 with, 7.4 with
+// one thread per cut.  Every FFN workgroup working it out for itself took 1.0
+// us of each launch.
 constexpr int kCutBlocks = 64;
 static_assert(kCutBlocks * 256 == 2 * kCuts * kCutSlots && kCutSlots == 8, "threads per stage, cut and slot");
 __device__ __forceinline__ void choose_cut(const CutArgs& a, int block) {
